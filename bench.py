@@ -121,7 +121,8 @@ TUNED_KEYS = (
     "stencil.pair_rows",
 )
 KERNEL_SOURCES = {
-    "fft": ("paper_1807_04638_amd/csrc/fft.hip", "paper_1807_04638_amd/csrc/fft_core.h",
+    "fft": ("paper_1807_04638_amd/csrc/fft.hip", "paper_1807_04638_amd/csrc/fft_rt.hip",
+            "paper_1807_04638_amd/csrc/fft_rt.h", "paper_1807_04638_amd/csrc/fft_core.h",
             "paper_1807_04638_amd/csrc/index_math.h"),
     "stencil": ("paper_1807_04638_amd/csrc/stencil.hip", "paper_1807_04638_amd/csrc/index_math.h"),
 }

@@ -275,7 +275,8 @@ int lddmm_profile_read(lddmm_ctx* ctx, const char** names, int64_t* counts, doub
  *                                           pencils of k1 and k1 + N1/2 of each pair)
  *   "fft.rows_rb"         1..64             rows per workgroup (split path)
  *   "fft.force_split"     0 | 1             split transform path even where a plane fits
- *   "fft.static"          0 | 1             compile-time kernels for power-of-two lengths
+ *   "fft.static"          0 | 1             compile-time kernels where they exist (0: the
+ *                                           run-time ones for every length)
  *   "fft.plane_grid"      0..65535          0: one (x1, x2) plane per workgroup; G > 0: G
  *                                           workgroups walk the planes (g, g + G, ...), loading
  *                                           the next plane while transforming the current one
@@ -288,11 +289,12 @@ int lddmm_profile_read(lddmm_ctx* ctx, const char** names, int64_t* counts, doub
  *                                           units), each transformed along x1 at half length;
  *                                           the x0 pencil pass merges the two halves (the first
  *                                           radix-2 step of the x1 transform) before its
- *                                           transform and splits them after.  Needs an even N1,
- *                                           compile-time kernels for the grid, no plane walk
- *                                           and an even fft.pencil_tb of 8 to 32; otherwise
+ *                                           transform and splits them after.  Where a half does
+ *                                           not fit the LDS, four or three units (rows x1 mod 4
+ *                                           or 3) in the same way.  Needs such a divisor of N1,
+ *                                           no plane walk and an even fft.pencil_tb; otherwise
  *                                           whole planes are used.  Default 1
- *   "fft.plane_halves_used" read-only: 1 if half planes are in use
+ *   "fft.plane_halves_used" read-only: 1 if planes are cut so
  *   "fft.fused"           read-only: 1 if the fused plane path is in use
  *   "fft.static_kernels"  read-only: number of passes using compile-time kernels
  *   "traj.policy"         read-only: 0 store-all, 1 checkpoint, 2 recompute

@@ -16,9 +16,12 @@
 //   pass 2  pencil: x0 forward, symbol, x0 inverse    spectrum in place
 //   pass 3  plane: columns (x1) inverse + rows (x2)   spectrum    -> real field
 // Split path: rows, x1 pencils, x0 pencils with symbol, x1 pencils, rows.
+// The fused path's kernels here have compile-time lengths (the common grids);
+// fft_rt.hip has those for every other length.
 #include <cmath>
 #include <cstring>
 
+#include "fft_rt.h"
 #include "lddmm.h"
 #include "lddmm_internal.h"
 
@@ -171,48 +174,6 @@ __device__ PlaneLds<T> carve(unsigned char* smem, int rows, const PlaneArgs<T>& 
   return L;
 }
 
-// One (x0, component) plane: real rows -> x2 spectrum -> x1 columns.
-template <typename T, int NT>
-__global__ void __launch_bounds__(NT) k_plane_fwd(const T* __restrict__ in, cplx<T>* __restrict__ spec,
-                                                   PlaneArgs<T> a) {
-  extern __shared__ __align__(16) unsigned char smem[];
-  const int x0 = blockIdx.x, comp = blockIdx.y;
-  PlaneLds<T> L = carve(smem, a.n1, a, true);
-  const cplx<T>* src = reinterpret_cast<const cplx<T>*>(in + comp * a.N + (long long)x0 * a.n1 * a.n2);
-  const int tot = a.n1 * a.H;
-  for (int idx = threadIdx.x; idx < tot; idx += blockDim.x) {
-    const int j1 = idx / a.H;
-    L.A[j1 * a.M + (idx - j1 * a.H)] = src[idx];
-  }
-  __syncthreads();
-  rows_r2c(L.A, a.n1, a.H, a.M, a.p2, L.tw2, L.twr, L.slot2);
-  lds_fft<T, false, true>(L.A, a.p1, a.M, a.M, 1, L.tw1);
-  cplx<T>* dst = spec + ((long long)comp * a.n0 + x0) * a.n1 * a.M;
-  const int tot2 = a.n1 * a.M;
-  for (int idx = threadIdx.x; idx < tot2; idx += blockDim.x) dst[idx] = L.A[idx];
-}
-
-// One (x0, component) plane: x1 columns inverse -> x2 rows inverse -> real rows.
-template <typename T, int NT>
-__global__ void __launch_bounds__(NT) k_plane_inv(const cplx<T>* __restrict__ spec, T* __restrict__ out,
-                                                   PlaneArgs<T> a) {
-  extern __shared__ __align__(16) unsigned char smem[];
-  const int x0 = blockIdx.x, comp = blockIdx.y;
-  PlaneLds<T> L = carve(smem, a.n1, a, true);
-  const cplx<T>* src = spec + ((long long)comp * a.n0 + x0) * a.n1 * a.M;
-  const int tot2 = a.n1 * a.M;
-  for (int idx = threadIdx.x; idx < tot2; idx += blockDim.x) L.A[idx] = src[idx];
-  __syncthreads();
-  lds_fft<T, true, true>(L.A, a.p1, a.M, a.M, 1, L.tw1);
-  rows_c2r(L.A, a.n1, a.H, a.M, a.p2, L.tw2, L.twr, L.slot2);
-  cplx<T>* dst = reinterpret_cast<cplx<T>*>(out + comp * a.N + (long long)x0 * a.n1 * a.n2);
-  const int tot = a.n1 * a.H;
-  for (int idx = threadIdx.x; idx < tot; idx += blockDim.x) {
-    const int j1 = idx / a.H;
-    dst[idx] = L.A[j1 * a.M + (idx - j1 * a.H)];
-  }
-}
-
 // Split path: `rb` consecutive rows (flat x0 * n1 + x1) per workgroup.
 template <typename T>
 __global__ void __launch_bounds__(256) k_rows_fwd(const T* __restrict__ in, cplx<T>* __restrict__ spec,
@@ -287,19 +248,16 @@ struct PencilArgs {
 // x0 plane of the spectrum is not (180 x 216 x 180: 9828 complex values).  On
 // aligned grids (128^3) the units keep the round-robin order, which measured
 // 1 % faster there.
-constexpr int kPlaneXcdRun = 2, kPencilXcdRun = 8;
+constexpr int kPencilXcdRun = 8;
 
-// MODE 0: forward only, 1: inverse only, 2: forward, symbol, inverse.
-template <typename T, int MODE, int NT>
+// x1 pencils of the split path, forward (INV = false) or inverse.
+template <typename T, bool INV, int NT>
 __global__ void __launch_bounds__(NT) k_pencil(cplx<T>* __restrict__ spec, PencilArgs<T> a) {
   extern __shared__ __align__(16) unsigned char smem[];
   const int n = a.pl.n, tb = a.tb;
   cplx<T>* A = reinterpret_cast<cplx<T>*>(smem);
   cplx<T>* tw = A + n * tb;
-  T* ksq0 = reinterpret_cast<T*>(tw + n);
   load_table(tw, a.tw, n);
-  if (MODE == 2)
-    for (int i = threadIdx.x; i < n; i += blockDim.x) ksq0[i] = a.ksq0[i];
   // runs of neighbouring tiles on one XCD where they share cache lines
   const int lin = a.xcd_run > 1 ? xcd_grouped(int(blockIdx.y * gridDim.x + blockIdx.x), int(gridDim.x * gridDim.y),
                                               a.xcd_run)
@@ -312,23 +270,7 @@ __global__ void __launch_bounds__(NT) k_pencil(cplx<T>* __restrict__ spec, Penci
     A[idx] = t < cnt ? base[(long long)j * a.es + t] : cplx<T>{T(0), T(0)};
   }
   __syncthreads();
-  if (MODE != 1) lds_fft<T, false, true>(A, a.pl, tb, tb, 1, tw);
-  if (MODE == 2) {
-    for (int idx = threadIdx.x; idx < n * tb; idx += blockDim.x) {
-      const int j = idx / tb, t = idx - j * tb;
-      if (t < cnt) {
-        const int q = q0 + t;
-        const int s1 = q / a.M, s2 = q - s1 * a.M;
-        const T base_sym = T(1) + a.alpha * (ksq0[j] + a.ksq1[s1] + a.ksq2[s2]);
-        T pw = base_sym;
-        for (int i = 1; i < a.s; ++i) pw *= base_sym;
-        const T f = a.op == LDDMM_OP_K ? a.scale / pw : a.scale * pw;
-        A[idx] = c_scale(A[idx], f);
-      }
-    }
-    __syncthreads();
-  }
-  if (MODE != 0) lds_fft<T, true, true>(A, a.pl, tb, tb, 1, tw);
+  lds_fft<T, INV, true>(A, a.pl, tb, tb, 1, tw);
   for (int idx = threadIdx.x; idx < n * tb; idx += blockDim.x) {
     const int j = idx / tb, t = idx - j * tb;
     if (t < cnt) base[(long long)j * a.es + t] = A[idx];
@@ -336,8 +278,8 @@ __global__ void __launch_bounds__(NT) k_pencil(cplx<T>* __restrict__ spec, Penci
 }
 
 // --------------------------------------------------------------------------
-// Compile-time variants for power-of-two lengths (same algorithm, same LDS
-// layout and spectrum layout as the generic kernels above; every index is a
+// Compile-time variants of the common lengths (same algorithm, same LDS
+// layout and spectrum layout as the run-time kernels; every index is a
 // constant shift and the stage loops unroll).
 // --------------------------------------------------------------------------
 // Stages I .. END-1 of the transform (in DIF order forward, DIT order inverse).
@@ -1201,13 +1143,9 @@ void rows_static(const FftPlan& p2, int RB, void*& f, void*& i) {
 }
 
 template <typename T>
-void* pencil_generic(int mode, int nt) {
-  if (nt == 512) return mode == 0 ? (void*)(PencilFn<T>)k_pencil<T, 0, 512>
-                      : mode == 1 ? (void*)(PencilFn<T>)k_pencil<T, 1, 512>
-                                  : (void*)(PencilFn<T>)k_pencil<T, 2, 512>;
-  return mode == 0 ? (void*)(PencilFn<T>)k_pencil<T, 0, 256>
-       : mode == 1 ? (void*)(PencilFn<T>)k_pencil<T, 1, 256>
-                   : (void*)(PencilFn<T>)k_pencil<T, 2, 256>;
+void* pencil_generic(bool inv, int nt) {
+  if (nt == 512) return inv ? (void*)(PencilFn<T>)k_pencil<T, true, 512> : (void*)(PencilFn<T>)k_pencil<T, false, 512>;
+  return inv ? (void*)(PencilFn<T>)k_pencil<T, true, 256> : (void*)(PencilFn<T>)k_pencil<T, false, 256>;
 }
 
 }  // namespace
@@ -1223,44 +1161,30 @@ int spectral_configure(SpectralPlan<T>& sp, const FftTuning& tune, std::string& 
   const size_t cb = sizeof(cplx<T>);
   const int n0 = sp.n0, n1 = sp.n1, H = sp.H, M = sp.M;
   const int tb = tune.pencil_tb;
-  const size_t tables = size_t(H + H / 2 + 1) * cb + size_t(H + 1) * sizeof(int);
-  size_t plane_lds = size_t(n1) * M * cb + size_t(n1) * cb + tables;
-  // half planes: compile-time kernels only, one unit per workgroup, pencil
-  // tiles of whole pairs
-  void* hk[4] = {nullptr, nullptr, nullptr, nullptr};
-  const int n1h = n1 / 2;
-  const size_t half_lds = size_t(n1h) * M * cb + size_t(n1h) * cb + tables;
-  if (tune.plane_halves && !tune.force_split && tune.plane_grid == 0 && tune.use_static && sp.tw1h &&
-      tune.pencil_threads == 256 && tb % 2 == 0 && half_lds <= sp.max_lds) {
-    if (tune.plane_threads == 512) plane_static_halves<T, 512>(sp.p2, sp.p1h, hk[0], hk[1], hk[2]);
-    if (tune.plane_threads == 1024) plane_static_halves<T, 1024>(sp.p2, sp.p1h, hk[0], hk[1], hk[2]);
-    hk[3] = pencil_static_pairs<T>(sp.p0, tb / 2);
-  }
-  const bool halves = hk[0] && hk[3];
-  if (halves) plane_lds = half_lds;
-  const bool fused = halves || (!tune.force_split && plane_lds <= sp.max_lds);
-  // the compile-time pencils also keep TB per-sequence symbol terms
-  const size_t p0 = (size_t(n0) * tb + n0) * cb + size_t(n0 + tb) * sizeof(T);
-  const size_t p1 = (size_t(n1) * tb + n1) * cb + size_t(n1 + tb) * sizeof(T);
-  const size_t rl = size_t(tune.rows_rb) * M * cb + tables;
-  if (p0 > sp.max_lds || (!fused && (p1 > sp.max_lds || rl > sp.max_lds))) {
-    err = "transform tiles exceed the LDS of a workgroup";
-    return LDDMM_EUNSUPPORTED;
-  }
-  void* k[8] = {nullptr, nullptr, nullptr, nullptr, nullptr, nullptr, nullptr, nullptr};
-  int nstatic = 0;
   const bool use_static = tune.use_static != 0;
-  // plane walk: compile-time plane kernels only
-  const bool walk = tune.plane_grid > 0;
-  int plane_grid = 0;
-  if (halves) {
-    k[KF_PLANE_FWD] = hk[0];
-    k[KF_PLANE_INV] = hk[1];
-    k[KF_PLANE_INV_ADD] = hk[2];
-    k[KF_PENCIL0] = hk[3];
-    nstatic += 2;
-  } else if (fused) {
-    if (use_static) {
+  const bool walk = tune.plane_grid > 0;  // plane walk: compile-time plane kernels only
+  const size_t tables = size_t(H + H / 2 + 1) * cb + size_t(H + 1) * sizeof(int);
+  auto unit_lds = [&](int rows, int row_stride) { return size_t(rows) * row_stride * cb + size_t(rows) * cb + tables; };
+  void* k[8] = {nullptr, nullptr, nullptr, nullptr, nullptr, nullptr, nullptr, nullptr};
+  int nstatic = 0, plane_grid = 0;
+  // units per plane: the plan's (half planes; quarters or thirds where a half does
+  // not fit the LDS), whole planes where asked for or with a plane walk
+  int xs = 1;
+  if (tune.plane_halves && !tune.force_split && !walk && sp.xs > 1 && tb % 2 == 0 &&
+      unit_lds(n1 / sp.xs, M) <= sp.max_lds)
+    xs = sp.xs;
+  const bool fused = xs > 1 || (!tune.force_split && unit_lds(n1, M) <= sp.max_lds);
+  bool plane_rt = false, pencil_rt = false;
+  size_t plane_lds = 0;
+  int lm = M;
+  if (fused) {
+    // compile-time plane kernels where instantiated, else the run-time ones
+    if (use_static && xs == 2) {
+      if (tune.plane_threads == 512)
+        plane_static_halves<T, 512>(sp.p2, sp.p1u, k[KF_PLANE_FWD], k[KF_PLANE_INV], k[KF_PLANE_INV_ADD]);
+      if (tune.plane_threads == 1024)
+        plane_static_halves<T, 1024>(sp.p2, sp.p1u, k[KF_PLANE_FWD], k[KF_PLANE_INV], k[KF_PLANE_INV_ADD]);
+    } else if (use_static && xs == 1) {
       if (tune.plane_threads == 512 && walk) plane_static<T, 512, true>(sp.p2, sp.p1, k[KF_PLANE_FWD], k[KF_PLANE_INV], k[KF_PLANE_INV_ADD]);
       if (tune.plane_threads == 512 && !walk) plane_static<T, 512, false>(sp.p2, sp.p1, k[KF_PLANE_FWD], k[KF_PLANE_INV], k[KF_PLANE_INV_ADD]);
       // the walk's extra registers spill with 1024 threads in FP64: not offered there
@@ -1268,19 +1192,53 @@ int spectral_configure(SpectralPlan<T>& sp, const FftTuning& tune, std::string& 
         if (tune.plane_threads == 1024 && walk) plane_static<T, 1024, true>(sp.p2, sp.p1, k[KF_PLANE_FWD], k[KF_PLANE_INV], k[KF_PLANE_INV_ADD]);
       if (tune.plane_threads == 1024 && (!walk || sizeof(T) != 4))
         plane_static<T, 1024, false>(sp.p2, sp.p1, k[KF_PLANE_FWD], k[KF_PLANE_INV], k[KF_PLANE_INV_ADD]);
+      if (k[KF_PLANE_FWD])
+        plane_grid = walk && (sizeof(T) == 4 || tune.plane_threads != 1024) ? tune.plane_grid : 0;
     }
+    plane_lds = unit_lds(n1 / xs, M);
     if (k[KF_PLANE_FWD]) {
       nstatic++;
-      plane_grid = walk && (sizeof(T) == 4 || tune.plane_threads != 1024) ? tune.plane_grid : 0;
     } else {
-      k[KF_PLANE_FWD] = tune.plane_threads == 256    ? (void*)(PlaneFwdFn<T>)k_plane_fwd<T, 256>
-                        : tune.plane_threads == 1024 ? (void*)(PlaneFwdFn<T>)k_plane_fwd<T, 1024>
-                                                     : (void*)(PlaneFwdFn<T>)k_plane_fwd<T, 512>;
-      k[KF_PLANE_INV] = tune.plane_threads == 256    ? (void*)(PlaneInvFn<T>)k_plane_inv<T, 256>
-                        : tune.plane_threads == 1024 ? (void*)(PlaneInvFn<T>)k_plane_inv<T, 1024>
-                                                     : (void*)(PlaneInvFn<T>)k_plane_inv<T, 512>;
+      plane_rt = true;
+      const bool big = has_radix16(xs > 1 ? sp.p1u : sp.p1) || has_radix16(sp.p2);
+      k[KF_PLANE_FWD] = (void*)rt_plane_fwd<T>(big);
+      k[KF_PLANE_INV] = k[KF_PLANE_INV_ADD] = (void*)rt_plane_inv<T>(big);
+      // an odd row stride (LDS banks) where it fits
+      if (unit_lds(n1 / xs, M | 1) <= sp.max_lds) lm = M | 1;
+      plane_lds = unit_lds(n1 / xs, lm);
     }
+  }
+  if (use_static && tune.pencil_threads == 256)
+    k[KF_PENCIL0] = xs == 2 ? pencil_static_pairs<T>(sp.p0, tb / 2) : xs == 1 ? pencil_static<T, 2>(sp.p0, tb) : nullptr;
+  if (k[KF_PENCIL0]) {
+    nstatic++;
   } else {
+    pencil_rt = true;
+    k[KF_PENCIL0] = (void*)rt_pencil<T>(xs, has_radix16(sp.p0));
+  }
+  // groups of xs sequences per pencil workgroup; the pencils also keep a symbol
+  // term per sequence
+  const int groups = tb / xs > 0 ? tb / xs : 1;
+  const size_t p0 = (size_t(n0) * groups * xs + n0) * cb + size_t(n0 + groups * xs) * sizeof(T);
+  const size_t p1 = (size_t(n1) * tb + n1) * cb + size_t(n1 + tb) * sizeof(T);
+  const size_t rl = size_t(tune.rows_rb) * M * cb + tables;
+  if (p0 > sp.max_lds || (!fused && (p1 > sp.max_lds || rl > sp.max_lds))) {
+    err = "transform tiles exceed the LDS of a workgroup";
+    return LDDMM_EUNSUPPORTED;
+  }
+  if ((plane_rt || pencil_rt) && size_t(n0) * n1 * M * cb >= size_t(1) << 32) {
+    // the run-time kernels' offsets inside a component (its context would not fit
+    // the device's memory)
+    err = "one component's spectrum exceeds 4 GiB";
+    return LDDMM_EUNSUPPORTED;
+  }
+  RtPlan r0, r1, r2;
+  if ((pencil_rt && !make_rt_plan(sp.p0, r0)) ||
+      (plane_rt && (!make_rt_plan(xs > 1 ? sp.p1u : sp.p1, r1) || !make_rt_plan(sp.p2, r2)))) {
+    err = "a transform length has too many factors";
+    return LDDMM_EUNSUPPORTED;
+  }
+  if (!fused) {
     const long long rows = (long long)n0 * n1;
     if (use_static && rows % tune.rows_rb == 0) rows_static<T>(sp.p2, tune.rows_rb, k[KF_ROWS_FWD], k[KF_ROWS_INV]);
     if (k[KF_ROWS_FWD]) {
@@ -1296,16 +1254,9 @@ int spectral_configure(SpectralPlan<T>& sp, const FftTuning& tune, std::string& 
     if (k[KF_PENCIL1F]) {
       nstatic++;
     } else {
-      k[KF_PENCIL1F] = pencil_generic<T>(0, tune.pencil_threads);
-      k[KF_PENCIL1I] = pencil_generic<T>(1, tune.pencil_threads);
+      k[KF_PENCIL1F] = pencil_generic<T>(false, tune.pencil_threads);
+      k[KF_PENCIL1I] = pencil_generic<T>(true, tune.pencil_threads);
     }
-  }
-  if (!halves) {
-    if (use_static && tune.pencil_threads == 256) k[KF_PENCIL0] = pencil_static<T, 2>(sp.p0, tb);
-    if (k[KF_PENCIL0])
-      nstatic++;
-    else
-      k[KF_PENCIL0] = pencil_generic<T>(2, tune.pencil_threads);
   }
   for (void* f : k)
     if (f && hipFuncSetAttribute((const void*)f, hipFuncAttributeMaxDynamicSharedMemorySize, int(sp.max_lds)) !=
@@ -1315,7 +1266,13 @@ int spectral_configure(SpectralPlan<T>& sp, const FftTuning& tune, std::string& 
     }
   sp.tune = tune;
   sp.fused = fused;
-  sp.halves = halves;
+  sp.units = xs;
+  sp.plane_rt = plane_rt;
+  sp.pencil_rt = pencil_rt;
+  sp.lm = lm;
+  sp.r0 = r0;
+  sp.r1 = r1;
+  sp.r2 = r2;
   sp.plane_grid = plane_grid;
   sp.plane_lds = plane_lds;
   sp.pencil0_lds = p0;
@@ -1324,6 +1281,33 @@ int spectral_configure(SpectralPlan<T>& sp, const FftTuning& tune, std::string& 
   sp.static_kernels = nstatic;
   for (int i = 0; i < 8; ++i) sp.kfn[i] = k[i];
   return 0;
+}
+
+// Threads of a run-time plane workgroup for units of `values` complex values: 1024
+// where at most two units share a compute unit's LDS (180 x 210 x 180 FP32, 76 KB:
+// 59 + 51 us a pass against 66 + 56 with 512; FP64, 153 KB: 129 + 113 against 136 +
+// 118), 512 below (128^3 FP64, 66 KB: 28.5 us against 33 with 1024; 160 x 140 x 150
+// FP32, 42 KB: 31 against 33 with 1024 and 40 with 256), 256 for units of a few rounds
+// (60 x 84 x 70: equal to 512, and 20 % faster than 1024).
+template <typename T>
+int rt_plane_threads(size_t values) {
+  return values * sizeof(cplx<T>) > 72 * 1024 ? 1024 : values > 1536 ? 512 : 256;
+}
+
+// Units that a plane is cut into (their tables are part of the plan): halves, or
+// quarters or thirds where a half does not fit the LDS; odd n1 gets thirds where
+// the whole plane does not fit.  1: whole planes only.
+template <typename T>
+int plane_units(int n1, int H, size_t max_lds) {
+  const size_t cb = sizeof(cplx<T>);
+  const size_t tables = size_t(H + H / 2 + 1) * cb + size_t(H + 1) * sizeof(int);
+  auto fits = [&](int xs) {
+    return n1 % xs == 0 && n1 / xs >= 4 && size_t(n1 / xs) * (H + 2) * cb + tables <= max_lds;
+  };
+  if (n1 % 2 != 0 && fits(1)) return 1;
+  for (int xs : {2, 4, 3})
+    if (fits(xs)) return xs;
+  return n1 % 2 == 0 && n1 >= 8 ? 2 : 1;
 }
 
 template <typename T>
@@ -1339,11 +1323,13 @@ FftTuning default_tuning(const SpectralPlan<T>& sp) {
   // half planes where compile-time kernels exist (spectral_configure falls back
   // to whole planes otherwise)
   t.plane_halves = 1;
-  if (sizeof(T) == 4 && sp.tw1h) {
+  void *f = nullptr, *i = nullptr, *ia = nullptr;
+  plane_static_halves<T, 512>(sp.p2, sp.p1u, f, i, ia);
+  if (f) {
     // small FP32 half planes (up to 64 x 65 complex) run best with 512 threads
-    void *f = nullptr, *i = nullptr, *ia = nullptr;
-    plane_static_halves<T, 512>(sp.p2, sp.p1h, f, i, ia);
-    if (f && size_t(sp.n1 / 2) * sp.M <= size_t(64) * 65) t.plane_threads = 512;
+    if (sizeof(T) == 4 && size_t(sp.n1 / 2) * sp.M <= size_t(64) * 65) t.plane_threads = 512;
+  } else {
+    t.plane_threads = rt_plane_threads<T>(size_t(sp.n1 / (sp.xs > 1 ? sp.xs : 1)) * sp.H);
   }
   int tb = int(256 / cb);
   while (tb > 1 && ((size_t(sp.n0) * tb + sp.n0) * cb + sp.n0 * sizeof(T) > sp.max_lds ||
@@ -1359,11 +1345,11 @@ FftTuning default_tuning(const SpectralPlan<T>& sp) {
   return t;
 }
 
-// Plans and the host image of the tables; device pointers are offsets into
+// Plans and the host image of the tables (`units`: with those of cut planes); device pointers are offsets into
 // the table block until spectral_place_tables sets its base.
 template <typename T>
-int spectral_plan_tables(SpectralPlan<T>& sp, const int n[3], size_t max_lds, std::string& err, TableBlob& blob,
-                         size_t off[12]) {
+int spectral_plan_tables(SpectralPlan<T>& sp, const int n[3], size_t max_lds, bool units, std::string& err,
+                         TableBlob& blob, size_t off[12]) {
   sp = SpectralPlan<T>();
   sp.n0 = n[0];
   sp.n1 = n[1];
@@ -1400,19 +1386,20 @@ int spectral_plan_tables(SpectralPlan<T>& sp, const int n[3], size_t max_lds, st
   off[5] = blob.put(k0);
   off[6] = blob.put(k1);
   off[7] = blob.put(k2);
-  // half-plane tables: the x1 transform of half length, the merge twiddles
-  // W_{n1}^{k1} and |k1|^2, |k1 + n1/2|^2 per slot of the half transform
-  if (n[1] % 2 == 0 && n[1] >= 8 && make_plan(n[1] / 2, sp.p1h)) {
-    const int h1 = n[1] / 2;
-    off[8] = blob.put(twiddles<T>(h1, h1));
-    std::vector<cplx<T>> wx(h1);
+  // unit tables: the x1 transform of length n1 / xs, the merge twiddles W_{n1}^{k1}
+  // and |k1 + p n1 / xs|^2, p < xs, per slot of the unit transform
+  sp.xs = units ? plane_units<T>(n[1], H, max_lds) : 1;
+  if (sp.xs > 1 && !make_plan(n[1] / sp.xs, sp.p1u)) sp.xs = 1;
+  if (sp.xs > 1) {
+    const int u1 = n[1] / sp.xs;
+    off[8] = blob.put(twiddles<T>(u1, u1));
+    std::vector<cplx<T>> wx(u1);
     std::vector<T> kx(n[1]);
-    for (int p = 0; p < h1; ++p) {
-      const int k = digit_reverse(sp.p1h, p);
+    for (int p = 0; p < u1; ++p) {
+      const int k = digit_reverse(sp.p1u, p);
       const double ang = -2.0 * M_PI * double(k) / double(n[1]);
       wx[p] = {T(std::cos(ang)), T(std::sin(ang))};
-      kx[p] = T(fold_sq(k, n[1]));
-      kx[h1 + p] = T(fold_sq(k + h1, n[1]));
+      for (int h = 0; h < sp.xs; ++h) kx[h * u1 + p] = T(fold_sq(k + h * u1, n[1]));
     }
     off[9] = blob.put(wx);
     off[10] = blob.put(kx);
@@ -1432,9 +1419,9 @@ void spectral_place_tables(SpectralPlan<T>& sp, unsigned char* base, const size_
   sp.ksq0 = static_cast<T*>(at(off[5]));
   sp.ksq1 = static_cast<T*>(at(off[6]));
   sp.ksq2 = static_cast<T*>(at(off[7]));
-  sp.tw1h = static_cast<cplx<T>*>(at(off[8]));
+  sp.tw1u = static_cast<cplx<T>*>(at(off[8]));
   sp.twx = static_cast<cplx<T>*>(at(off[9]));
-  sp.ksq1x = static_cast<T*>(at(off[10]));
+  sp.ksq1u = static_cast<T*>(at(off[10]));
 }
 
 template <typename T>
@@ -1446,7 +1433,7 @@ template <typename T>
 int spectral_init(SpectralPlan<T>& sp, const int n[3], size_t max_lds, std::string& err) {
   TableBlob blob;
   size_t off[12];
-  int rc = spectral_plan_tables(sp, n, max_lds, err, blob, off);
+  int rc = spectral_plan_tables(sp, n, max_lds, true, err, blob, off);
   if (rc) return rc;
   void* tables = nullptr;
   if (hipMalloc(&tables, blob.host.size()) != hipSuccess) {
@@ -1476,10 +1463,17 @@ int spectral_init_in(SpectralPlan<T>& sp, const int n[3], int ncomp, size_t max_
                      std::string& err) {
   TableBlob blob;
   size_t off[12];
-  int rc = spectral_plan_tables(sp, n, max_lds, err, blob, off);
+  int rc = spectral_plan_tables(sp, n, max_lds, true, err, blob, off);
   if (rc) return rc;
-  const size_t tab = (blob.host.size() + 255) & ~size_t(255);
-  const size_t need = tab + spectrum_bytes(sp, ncomp);
+  size_t tab = (blob.host.size() + 255) & ~size_t(255);
+  size_t need = tab + spectrum_bytes(sp, ncomp);
+  if (need > region_bytes && n[1] % 2 != 0 && sp.xs > 1) {
+    // thirds of an odd plane are an option: without their tables it may still fit
+    blob = TableBlob();
+    if ((rc = spectral_plan_tables(sp, n, max_lds, false, err, blob, off))) return rc;
+    tab = (blob.host.size() + 255) & ~size_t(255);
+    need = tab + spectrum_bytes(sp, ncomp);
+  }
   if (need > region_bytes) {
     err = "grid " + std::to_string(n[0]) + "x" + std::to_string(n[1]) + "x" + std::to_string(n[2]) + " with " +
           std::to_string(ncomp) + " component(s) needs " + std::to_string(need) +
@@ -1512,86 +1506,132 @@ void spectral_free(SpectralPlan<T>& sp) {
   sp = SpectralPlan<T>();
 }
 
-// Neighbouring pencil tiles share cache lines unless every tile's run starts on
-// a 128-byte line: then they take runs of kPencilXcdRun per XCD.
-template <typename T>
-int pencil_xcd_run(const PencilArgs<T>& k) {
-  const long long c = sizeof(cplx<T>);
-  return xcd_run_if_split(k.tb * c, k.es * c, k.hs * c, k.outer_stride * c, kPencilXcdRun);
-}
-
 template <typename T>
 void spectral_apply(const SpectralPlan<T>& sp, const T* in, T* out, int ncomp, double alpha, int s, int op,
                     hipStream_t st, Profiler* prof, const T* add, double add_scale, double out_scale) {
+  const FftTuning& tu = sp.tune;
+  const int xs = sp.units;
+  // units of a plane share the cache line at a row's end unless rows are whole lines
+  const int plane_run = xs > 1 ? xcd_run_if_split((long long)sp.n2 * sizeof(T), 0, 0, 0, xs) : 1;
+  const int P = sp.n1 * sp.M;
+  const T scale = T(out_scale / (double(sp.n0) * sp.n1 * sp.n2));  // the inverse's 1/N and the caller's factor
+  // x0 pencils: groups of the xs sequences that share a slot of the units' spectra
+  const int groups = tu.pencil_tb / xs > 0 ? tu.pencil_tb / xs : 1, nin = P / xs, hs = xs > 1 ? nin : 0;
+  const dim3 g0((nin + groups - 1) / groups, ncomp);
+  const long long c = sizeof(cplx<T>);
+  // neighbouring pencil tiles share cache lines unless every tile's run starts on a
+  // 128-byte line
+  const int pencil_run =
+      xcd_run_if_split(groups * c, P * c, hs * c, (long long)sp.n0 * P * c, kPencilXcdRun);
+  auto launch_pencil0 = [&]() {
+    KernelTimer t(prof, "fft_pencil_symbol");
+    if (sp.pencil_rt) {
+      RtPencilArgs<T> a;
+      a.threads = tu.pencil_threads;
+      a.r0 = sp.r0;
+      a.es = P;
+      a.nin = nin;
+      a.outer_stride = (long long)sp.n0 * P;
+      a.tb = groups;
+      a.inv_tb = 1.0f / float(groups);
+      a.inv_ts = 1.0f / float(groups * xs);
+      a.inv_M = 1.0f / float(sp.M);
+      a.hs = hs;
+      a.n1u = sp.n1 / xs;
+      a.M = sp.M;
+      a.tw = sp.tw0;
+      a.twx = sp.twx;
+      a.alpha = T(alpha);
+      a.s = s;
+      a.op = op;
+      a.scale = scale;
+      a.ksq0 = sp.ksq0;
+      a.ksq1 = xs > 1 ? sp.ksq1u : sp.ksq1;
+      a.ksq2 = sp.ksq2;
+      a.xcd_run = pencil_run;
+      LDDMM_LAUNCH(t.start, t.stop, ((RtPencilFn<T>)sp.kfn[KF_PENCIL0]), g0, tu.pencil_threads, sp.pencil0_lds, st, sp.spec, a);
+      return;
+    }
+    PencilArgs<T> a;
+    a.pl = sp.p0;
+    a.es = P;
+    a.nin = nin;
+    a.outer_stride = (long long)sp.n0 * P;
+    a.tb = groups;
+    a.tw = sp.tw0;
+    a.M = sp.M;
+    a.alpha = T(alpha);
+    a.s = s;
+    a.op = op;
+    a.scale = scale;
+    a.ksq0 = sp.ksq0;
+    a.ksq1 = xs > 1 ? sp.ksq1u : sp.ksq1;
+    a.ksq2 = sp.ksq2;
+    a.hs = hs;
+    a.k1half = xs > 1 ? sp.n1 / xs : 0;
+    a.twx = xs > 1 ? sp.twx : nullptr;
+    a.xcd_run = pencil_run;
+    LDDMM_LAUNCH(t.start, t.stop, ((PencilFn<T>)sp.kfn[KF_PENCIL0]), g0, tu.pencil_threads, sp.pencil0_lds, st, sp.spec, a);
+  };
+
+  if (sp.plane_rt) {
+    RtPlaneArgs<T> a;
+    a.threads = tu.plane_threads;
+    a.n0 = sp.n0;
+    a.n1u = sp.n1 / xs;
+    a.H = sp.H;
+    a.M = sp.M;
+    a.LM = sp.lm;
+    a.xs = xs;
+    a.N = (long long)sp.n0 * sp.n1 * sp.n2;
+    a.r1 = sp.r1;
+    a.r2 = sp.r2;
+    a.inv_n1u = 1.0f / float(a.n1u);
+    a.inv_H = 1.0f / float(sp.H);
+    a.tw1 = xs > 1 ? sp.tw1u : sp.tw1;
+    a.tw2 = sp.tw2;
+    a.twr = sp.twr;
+    a.slot2 = sp.slot2;
+    a.add = add;
+    a.add_scale = T(add_scale);
+    a.xcd_run = plane_run;
+    const dim3 gp(xs * sp.n0, ncomp);
+    {
+      KernelTimer t(prof, "fft_plane_fwd");
+      LDDMM_LAUNCH(t.start, t.stop, ((RtPlaneFwdFn<T>)sp.kfn[KF_PLANE_FWD]), gp, tu.plane_threads, sp.plane_lds, st, in, sp.spec, a);
+    }
+    launch_pencil0();
+    KernelTimer t(prof, add ? "fft_plane_inv_add" : "fft_plane_inv");
+    LDDMM_LAUNCH(t.start, t.stop, ((RtPlaneInvFn<T>)sp.kfn[KF_PLANE_INV]), gp, tu.plane_threads, sp.plane_lds, st, sp.spec, out, a);
+    return;
+  }
   PlaneArgs<T> pa;
   pa.n0 = sp.n0;
   pa.n1 = sp.n1;
   pa.n2 = sp.n2;
   pa.H = sp.H;
   pa.M = sp.M;
-  pa.planes = ncomp * sp.n0;
+  pa.planes = xs * ncomp * sp.n0;
   pa.N = (long long)sp.n0 * sp.n1 * sp.n2;
   pa.p1 = sp.p1;
   pa.p2 = sp.p2;
-  pa.tw1 = sp.tw1;
+  pa.tw1 = xs > 1 ? sp.tw1u : sp.tw1;
   pa.tw2 = sp.tw2;
   pa.twr = sp.twr;
   pa.slot2 = sp.slot2;
   pa.add = add;
   pa.add_scale = T(add_scale);
-  // half planes share the cache line at a row's end unless rows are whole lines
-  pa.xcd_run = sp.halves ? xcd_run_if_split((long long)sp.n2 * sizeof(T), 0, 0, 0, kPlaneXcdRun) : 1;
-  const FftTuning& tu = sp.tune;
-
-  const int P = sp.n1 * sp.M;
-  PencilArgs<T> k0;
-  k0.pl = sp.p0;
-  k0.es = P;
-  k0.nin = P;
-  k0.outer_stride = (long long)sp.n0 * P;
-  k0.tb = tu.pencil_tb;
-  k0.tw = sp.tw0;
-  k0.M = sp.M;
-  k0.alpha = T(alpha);
-  k0.s = s;
-  k0.op = op;
-  k0.scale = T(out_scale / (double(sp.n0) * sp.n1 * sp.n2));  // the inverse's 1/N and the caller's factor
-  k0.ksq0 = sp.ksq0;
-  k0.ksq1 = sp.ksq1;
-  k0.ksq2 = sp.ksq2;
-  k0.hs = 0;
-  k0.k1half = 0;
-  k0.twx = nullptr;
-  dim3 g0((P + tu.pencil_tb - 1) / tu.pencil_tb, ncomp);
-  if (sp.halves) {
-    // units (component, x0, h): the x1 transform of half length; pencils in pairs
-    pa.planes = 2 * ncomp * sp.n0;
-    pa.tw1 = sp.tw1h;
-    const int tbp = tu.pencil_tb / 2, pairs = P / 2;
-    k0.nin = pairs;
-    k0.tb = tbp;
-    k0.hs = pairs;
-    k0.k1half = sp.n1 / 2;
-    k0.ksq1 = sp.ksq1x;
-    k0.twx = sp.twx;
-    g0 = dim3((pairs + tbp - 1) / tbp, ncomp);
-  }
-  k0.xcd_run = pencil_xcd_run(k0);
-  const PencilFn<T> pencil0 = (PencilFn<T>)sp.kfn[KF_PENCIL0];
-
+  pa.xcd_run = plane_run;
   if (sp.fused) {
     // plane walk: at most plane_grid workgroups, never more than there are planes
     const dim3 gp = sp.plane_grid > 0 ? dim3(unsigned(sp.plane_grid < pa.planes ? sp.plane_grid : pa.planes))
-                                      : dim3(sp.halves ? 2 * sp.n0 : sp.n0, ncomp);
+                                      : dim3(xs * sp.n0, ncomp);
     {
       KernelTimer t(prof, "fft_plane_fwd");
       LDDMM_LAUNCH(t.start, t.stop, ((PlaneFwdFn<T>)sp.kfn[KF_PLANE_FWD]), gp, tu.plane_threads, sp.plane_lds, st, in, sp.spec, pa);
     }
-    {
-      KernelTimer t(prof, "fft_pencil_symbol");
-      LDDMM_LAUNCH(t.start, t.stop, pencil0, g0, tu.pencil_threads, sp.pencil0_lds, st, sp.spec, k0);
-    }
-    if (add && sp.kfn[KF_PLANE_INV_ADD]) {
+    launch_pencil0();
+    if (add) {
       // the addend rides on the inverse plane pass: out = add + add_scale * K in
       KernelTimer t(prof, "fft_plane_inv_add");
       LDDMM_LAUNCH(t.start, t.stop, ((PlaneInvFn<T>)sp.kfn[KF_PLANE_INV_ADD]), gp, tu.plane_threads, sp.plane_lds, st, sp.spec, out, pa);
@@ -1601,16 +1641,17 @@ void spectral_apply(const SpectralPlan<T>& sp, const T* in, T* out, int ncomp, d
       KernelTimer t(prof, "fft_plane_inv");
       LDDMM_LAUNCH(t.start, t.stop, ((PlaneInvFn<T>)sp.kfn[KF_PLANE_INV]), gp, tu.plane_threads, sp.plane_lds, st, sp.spec, out, pa);
     }
-    if (add) launch_axpbyz<T>((long long)ncomp * pa.N, 1.0, add, add_scale, out, out, st, prof);
     return;
   }
-  PencilArgs<T> k1 = k0;
+  PencilArgs<T> k1{};
   k1.pl = sp.p1;
   k1.es = sp.M;
   k1.nin = sp.M;
   k1.outer_stride = (long long)sp.n1 * sp.M;
+  k1.tb = tu.pencil_tb;
   k1.tw = sp.tw1;
-  k1.xcd_run = pencil_xcd_run(k1);
+  k1.M = sp.M;
+  k1.xcd_run = xcd_run_if_split(k1.tb * c, k1.es * c, 0, k1.outer_stride * c, kPencilXcdRun);
   const dim3 g1((sp.M + tu.pencil_tb - 1) / tu.pencil_tb, ncomp * sp.n0);
   const long long rows = (long long)sp.n0 * sp.n1;
   const dim3 gr((unsigned)((rows + tu.rows_rb - 1) / tu.rows_rb), ncomp);
@@ -1622,10 +1663,7 @@ void spectral_apply(const SpectralPlan<T>& sp, const T* in, T* out, int ncomp, d
     KernelTimer t(prof, "fft_pencil_x1_fwd");
     LDDMM_LAUNCH(t.start, t.stop, ((PencilFn<T>)sp.kfn[KF_PENCIL1F]), g1, tu.pencil_threads, sp.pencil1_lds, st, sp.spec, k1);
   }
-  {
-    KernelTimer t(prof, "fft_pencil_symbol");
-    LDDMM_LAUNCH(t.start, t.stop, pencil0, g0, tu.pencil_threads, sp.pencil0_lds, st, sp.spec, k0);
-  }
+  launch_pencil0();
   {
     KernelTimer t(prof, "fft_pencil_x1_inv");
     LDDMM_LAUNCH(t.start, t.stop, ((PencilFn<T>)sp.kfn[KF_PENCIL1I]), g1, tu.pencil_threads, sp.pencil1_lds, st, sp.spec, k1);

@@ -1,0 +1,116 @@
+// fft_rt.h - transform passes for lengths known at run time (any product of 2,
+// 3, 5, 7): what the kernels of fft_rt.hip take and how their launch is planned.
+//
+// The (x1, x2) planes of the fused path are cut into XS units, unit h holding the
+// x1 rows XS m + h: n1 / XS rows, transformed along x1 at length n1 / XS.  The x0
+// pencil pass takes the XS partial spectra at one (k1, k2) slot together, forms
+// the pencils of k1, k1 + n1 / XS, ... (the first radix-XS step of the x1 transform
+// by decimation in x1) as it loads and undoes that as it stores.  XS = 1: whole
+// planes.
+#pragma once
+
+#include "fft_core.h"
+#include "index_math.h"
+
+namespace lddmm {
+
+// One stage of a run-time plan with what its kernels would otherwise divide for.
+struct RtStage {
+  int R;      // radix
+  int S;      // element stride inside a sub-block: L / R
+  int L;      // sub-block length
+  int tws;    // twiddle step n / L
+  float invS; // 1 / S (index_quot)
+};
+
+constexpr int kRtStages = 8;  // lengths whose pencil fits the LDS (20480 values) have at most 7
+
+struct RtPlan {
+  int n, nf;
+  RtStage st[kRtStages];
+};
+
+// Run-time form of a plan; false if it has more stages than the kernels take.
+inline bool make_rt_plan(const FftPlan& pl, RtPlan& r) {
+  r = RtPlan{};
+  r.n = pl.n;
+  r.nf = pl.nf;
+  if (pl.nf < 1 || pl.nf > kRtStages) return false;
+  int L = pl.n;
+  for (int i = 0; i < pl.nf; ++i) {
+    RtStage& s = r.st[i];
+    s.R = pl.radix[i];
+    s.L = L;
+    s.S = L / s.R;
+    s.tws = pl.n / L;
+    s.invS = 1.0f / float(s.S);
+    L = s.S;
+  }
+  return true;
+}
+
+// True if a plan holds a radix-16 stage: those take the kernels' BIG form (the
+// others keep the registers of a radix-9 butterfly).
+inline bool has_radix16(const FftPlan& pl) {
+  for (int i = 0; i < pl.nf; ++i)
+    if (pl.radix[i] == 16) return true;
+  return false;
+}
+
+template <typename T>
+struct RtPlaneArgs {
+  int threads;          // of a workgroup
+  int n0, n1u, H, M;    // n1u = n1 / XS rows per unit
+  int LM;               // row stride in the LDS (odd: rows one below the other miss each other's banks)
+  int xs;
+  long long N;          // n0 * n1 * n2
+  RtPlan r1, r2;        // lengths n1u and H
+  float inv_n1u, inv_H; // index_quot
+  const cplx<T>* tw1;
+  const cplx<T>* tw2;
+  const cplx<T>* twr;
+  const int* slot2;
+  const T* add;         // inverse pass: out = add + add_scale * (transform) where not null
+  T add_scale;
+  int xcd_run;          // units per XCD run (xcd_grouped); 1: round-robin order
+};
+
+template <typename T>
+struct RtPencilArgs {
+  int threads;             // of a workgroup
+  RtPlan r0;
+  int es;                  // element stride (complex units)
+  int nin;                 // groups of XS sequences per component
+  long long outer_stride;  // complex units between components
+  int tb;                  // groups per workgroup
+  float inv_tb, inv_ts, inv_M;
+  int hs;                  // offset of the next unit's spectrum: n1u * M
+  int n1u, M;
+  const cplx<T>* tw;
+  const cplx<T>* twx;      // W_{n1}^{k1} per slot of the unit transform (XS > 1)
+  T alpha;
+  int s, op;
+  T scale;
+  const T* ksq0;
+  const T* ksq1;           // |k1 + p n1u|^2 at p * n1u + slot
+  const T* ksq2;
+  int xcd_run;
+};
+
+template <typename T>
+using RtPlaneFwdFn = void (*)(const T*, cplx<T>*, RtPlaneArgs<T>);
+template <typename T>
+using RtPlaneInvFn = void (*)(const cplx<T>*, T*, RtPlaneArgs<T>);
+template <typename T>
+using RtPencilFn = void (*)(cplx<T>*, RtPencilArgs<T>);
+
+// Kernel entry points (fft_rt.hip).  Plane kernels take any workgroup of up to
+// 1024 threads, pencils up to 512.
+template <typename T>
+RtPlaneFwdFn<T> rt_plane_fwd(bool big);
+template <typename T>
+RtPlaneInvFn<T> rt_plane_inv(bool big);
+template <typename T>
+RtPencilFn<T> rt_pencil(int xs, bool big);  // xs 1 to 4
+
+}  // namespace lddmm

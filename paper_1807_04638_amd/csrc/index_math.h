@@ -6,6 +6,7 @@
 //   periodic_next / periodic_prev  neighbours on the periodic grid
 //   xcd_grouped, xcd_run_if_split  unit of a block so that each XCD takes runs
 //                                  of consecutive units that share cache lines
+//   index_quot                     integer quotient by a float reciprocal
 //   row_lanes                      x2 neighbours inside a row of lanes of the
 //                                  row-vectorised stencils
 //   sl_axis                        cell and weight of a displaced point along one
@@ -105,6 +106,20 @@ LDI_HD int xcd_grouped(int b, int B, int g) {
 // 1 (round-robin order).
 inline int xcd_run_if_split(long long a, long long b, long long c, long long d, int run) {
   return (a % 128 == 0 && b % 128 == 0 && c % 128 == 0 && d % 128 == 0) ? 1 : run;
+}
+
+// b / d for 0 <= b < 2^20 and 1 <= d < 2^20 from inv = 1.0f / d: the product of
+// b + 1/2 with the rounded reciprocal stays within b 2^-22 / d of (b + 1/2) / d,
+// which is at least 1 / 2d away from every integer.
+LDI_HD int index_quot(int b, float inv) { return int((float(b) + 0.5f) * inv); }
+// a * b of indices below 2^23: the 24-bit multiply issues at four times the rate of
+// the 32-bit one.
+LDI_HD int mul24(int a, int b) {
+#if defined(__HIP_DEVICE_COMPILE__)
+  return __mul24(a, b);
+#else
+  return a * b;
+#endif
 }
 
 LDI_HD int periodic_next(int i, int n) { return i + 1 == n ? 0 : i + 1; }

@@ -789,7 +789,7 @@ class Engine {
     if (reps <= 0) reps = 5;
     (void)hipStreamSynchronize(st);
     const FftTuning start = sp.tune;
-    const bool start_halves = sp.halves;  // in use, not only requested
+    const bool start_halves = (sp.units > 1);  // in use, not only requested
     FftTuning best = start;
     float best_ms = -1.f, start_ms = -1.f;
     int count = 0;
@@ -818,7 +818,7 @@ class Engine {
           t.plane_halves = gi == 0 ? 1 : 0;
           std::string msg;
           if (spectral_configure(sp, t, msg) != 0) continue;
-          if (gi == 0 && !sp.halves) continue;  // no half-plane kernels for this shape
+          if (gi == 0 && !(sp.units > 1)) continue;  // no half-plane kernels for this shape
           // each K application is followed by a tangent stage, as in the sweeps:
           // timed alone, back to back, the shapes rank differently than in use
           applyK(W, Z);
@@ -1443,7 +1443,7 @@ class Engine {
     else if (k == "fft.plane_halves")
       *value = t.plane_halves;
     else if (k == "fft.plane_halves_used")
-      *value = sp.halves ? 1 : 0;
+      *value = (sp.units > 1) ? 1 : 0;
     else if (k == "traj.policy")
       *value = traj_policy;
     else if (k == "traj.every")

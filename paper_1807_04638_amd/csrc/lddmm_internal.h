@@ -9,6 +9,7 @@
 #include <vector>
 
 #include "fft_core.h"
+#include "fft_rt.h"
 #include "index_math.h"
 
 namespace lddmm {
@@ -107,12 +108,16 @@ struct SpectralPlan {
   cplx<T>* spec = nullptr;                   // workspace: 3 * n0 * n1 * M complex
   void* table_mem = nullptr;                 // device block holding the tables above
   bool owns_memory = true;                   // false: tables and spectrum live in a caller's region
-  FftPlan p1h{};                             // length n1 / 2 (half planes; n = 0 when n1 is odd)
-  cplx<T>* tw1h = nullptr;                   // exp(-2 pi i m / (n1 / 2))
-  cplx<T>* twx = nullptr;                    // exp(-2 pi i k1 / n1) per slot of the half transform
-  T* ksq1x = nullptr;                        // |k1|^2, then |k1 + n1/2|^2, per slot of the half transform
-  bool fused = false;                        // (x2, x1) plane fits one workgroup's LDS
-  bool halves = false;                       // half planes in use
+  int xs = 1;                                // units a plane can be cut into (2: half planes; tables below)
+  FftPlan p1u{};                             // length n1 / xs (n = 0: whole planes only)
+  cplx<T>* tw1u = nullptr;                   // exp(-2 pi i m / (n1 / xs))
+  cplx<T>* twx = nullptr;                    // exp(-2 pi i k1 / n1) per slot of the unit transform
+  T* ksq1u = nullptr;                        // |k1 + p n1 / xs|^2 at p n1 / xs + slot of the unit transform
+  bool fused = false;                        // (x2, x1) plane or unit fits one workgroup's LDS
+  int units = 1;                             // units per plane in use (1: whole planes)
+  bool plane_rt = false, pencil_rt = false;  // run-time kernels (fft_rt.hip) in use
+  int lm = 0;                                // LDS row stride of the run-time plane kernels
+  RtPlan r0{}, r1{}, r2{};                   // their plans: lengths n0, n1 / units, H
   size_t plane_lds = 0, pencil0_lds = 0, pencil1_lds = 0, rows_lds = 0;
   size_t max_lds = 0;                        // LDS bytes available to one workgroup
   FftTuning tune{};

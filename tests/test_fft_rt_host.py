@@ -1,0 +1,80 @@
+"""The run-time transform kernels on the host (one host thread per lane, address
+sanitizer, poisoned LDS) against numpy.fft, over lengths of every radix, one and
+several stages, odd rows, ragged tiles and each number of units per plane."""
+
+import os
+import shutil
+import subprocess
+
+import numpy as np
+import pytest
+
+HERE = os.path.dirname(os.path.abspath(__file__))
+ROOT = os.path.dirname(HERE)
+
+# n0, n1, n2, components, units per plane, groups per pencil workgroup, lanes, XCD run, s, op (0 K, 1 L), add
+CASES = [
+    ((6, 10, 14), 1, 2, 5, 32, 1, 2, 0, 0),     # x2: one stage of radix 7; x0 two stages
+    ((4, 7, 4), 1, 1, 3, 32, 1, 1, 0, 1),       # whole odd planes, H = 2, one stage everywhere
+    ((5, 12, 6), 3, 4, 4, 32, 2, 2, 1, 1),      # quarters, single-stage x0, H = 3
+    ((15, 9, 10), 1, 3, 4, 32, 8, 3, 0, 0),     # thirds, ragged last tile
+    ((21, 20, 70), 1, 2, 16, 64, 8, 2, 0, 1),   # H = 35 (odd)
+    ((18, 16, 36), 1, 2, 8, 64, 1, 2, 1, 0),    # radix 9 and 2
+    ((16, 30, 30), 1, 2, 16, 64, 2, 2, 0, 0),   # radices 2, 3, 5; x0 = 16 (8 x 2)
+    ((4, 256, 8), 1, 2, 4, 64, 1, 2, 0, 0),     # a radix-16 stage along x1
+    ((128, 4, 4), 1, 1, 1, 32, 1, 2, 0, 1),     # a radix-16 stage along x0, one pencil per tile
+    ((24, 28, 50), 1, 4, 3, 64, 4, 2, 0, 0),    # quarters of 7 rows, H = 25
+]
+
+
+@pytest.fixture(scope="module")
+def exe(tmp_path_factory):
+    cc = shutil.which("g++")
+    if cc is None:
+        pytest.skip("g++ not available")
+    out = str(tmp_path_factory.mktemp("fftrt") / "fft_rt_host")
+    subprocess.run([cc, "-O1", "-std=c++17", "-pthread", "-fsanitize=address,undefined", "-fno-sanitize-recover=all",
+                    "-I", os.path.join(HERE, "native", "hip_host"), "-I",
+                    os.path.join(ROOT, "paper_1807_04638_amd", "csrc"), "-I", os.path.join(ROOT, "include"), "-x", "c++",
+                    os.path.join(HERE, "native", "fft_rt_host.cpp"), "-o", out], check=True)
+    return out
+
+
+@pytest.mark.parametrize("f64", [1, 0])
+@pytest.mark.parametrize("case", CASES, ids=lambda c: "x".join(map(str, c[0])) + f"-{c[2]}")
+def test_passes_match_numpy(exe, case, f64):
+    n, ncomp, xs, tb, lanes, run, s, op, add = case
+    rng = np.random.default_rng(sum(n))
+    f = rng.standard_normal((ncomp,) + n)
+    q = rng.standard_normal((ncomp,) + n)
+    if not f64:
+        f, q = f.astype(np.float32).astype(np.float64), q.astype(np.float32).astype(np.float64)
+    args = [*n, ncomp, xs, tb, lanes, run, s, op, f64, add]
+    r = subprocess.run([exe] + [str(int(a)) for a in args], input=f.tobytes() + (q.tobytes() if add else b""),
+                       capture_output=True, timeout=120)
+    assert r.returncode == 0, r.stderr.decode()[-2000:]
+    got = np.frombuffer(r.stdout).reshape(f.shape)
+    k2 = sum(np.meshgrid(*[np.fft.fftfreq(m, 1.0 / m) ** 2 for m in n], indexing="ij"))
+    sym = (1.0 + 0.0025 * k2) ** (s if op else -s)
+    ref = np.fft.ifftn(np.fft.fftn(f, axes=(1, 2, 3)) * sym, axes=(1, 2, 3)).real
+    if add:
+        ref = q + 0.3 * ref
+    # rounding of about 2 log2(N) stages on values up to the symbol's range times the input's
+    eps = 2.3e-16 if f64 else 1.2e-7
+    tol = 8 * eps * np.log2(np.prod(n)) * max(1.0, np.sqrt(np.mean(sym**2)))
+    assert np.linalg.norm(got - ref) <= tol * np.linalg.norm(f)
+
+
+def test_quotient_by_reciprocal_is_exact(tmp_path):
+    cc = shutil.which("g++")
+    if cc is None:
+        pytest.skip("g++ not available")
+    src = tmp_path / "q.cpp"
+    src.write_text('#include <initializer_list>\n#include "index_math.h"\nint main() { for (int d = 1; d < 2048; ++d) { const float i = 1.0f / float(d);'
+                   "for (int b = 0; b < (1 << 20); b += (b < 4096 ? 1 : 97)) { const int q = b / d;"
+                   "for (int x : {b, q * d, q * d + d - 1}) if (x < (1 << 20) && lddmm::index_quot(x, i) != x / d) return 1; }"
+                   "} return 0; }\nvoid __syncthreads() {}\n")
+    exe = str(tmp_path / "q")
+    subprocess.run([cc, "-O2", "-std=c++17", "-I", os.path.join(HERE, "native", "hip_host"), "-I",
+                    os.path.join(ROOT, "paper_1807_04638_amd", "csrc"), str(src), "-o", exe], check=True)
+    assert subprocess.run([exe]).returncode == 0

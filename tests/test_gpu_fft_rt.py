@@ -1,0 +1,62 @@
+"""The run-time transform kernels against the oracle: halves, thirds, quarters and
+whole planes, odd rows, every radix, single-stage axes and ragged pencil tiles, in
+both precisions, for vector and scalar fields.  Tolerances as for the operators of
+the other parity tests (FP64 1e-12, FP32 2e-6, L by its symbol's growth)."""
+
+import numpy as np
+import pytest
+import torch
+
+import oracle as O
+from synth import random_field
+from test_gpu_parity import DTYPES, TOL, T, l_tol, make, rel, rounded, say
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.mark.parametrize("n, opts, cut", [
+    ((24, 28, 50), {}, 1),                                            # halves of 14 rows, H = 25
+    ((9, 8, 6), {}, 1),                                               # the smallest halves, H = 3, one stage along x0
+    ((10, 45, 30), {}, 0),                                            # odd planes stay whole
+    ((4, 7, 4), {}, 0),                                               # one stage on every axis
+    ((63, 70, 90), {"fft.pencil_tb": 6}, 1),                          # ragged tiles of 3 groups
+    ((60, 84, 70), {"fft.plane_threads": 256, "fft.pencil_threads": 512}, 1),
+    ((30, 36, 42), {"fft.plane_halves": 0}, 0),                       # whole even planes
+    ((180, 210, 180), {}, 1),                                         # halves of 153 KB in FP64
+    ((128, 16, 128), {"fft.static": 0}, 1),                           # radix 16 along x0
+    ((12, 256, 32), {"fft.static": 0}, 1),                            # and along x1
+    ((8, 320, 288), {}, 1),                                           # quarters in FP32, split passes in FP64
+    ((6, 256, 256), {}, 1),                                           # halves in FP32, quarters in FP64
+    ((5, 225, 240), {}, 1),                                           # thirds
+])
+@pytest.mark.parametrize("dtype", DTYPES)
+def test_run_time_kernels(n, opts, cut, dtype):
+    R, p = make(n, dtype, alpha=0.0025)
+    for k, v in opts.items():
+        R.set_option(k, v)
+    used = R.get_option("fft.plane_halves_used")
+    say(f"  {opts} cut={used} fused={R.get_option('fft.fused')} static={R.get_option('fft.static_kernels')}")
+    if R.get_option("fft.fused"):
+        assert used == cut
+    f = rounded(random_field(n, 31, kc=max(n) / 4), dtype)
+    Lf = O.apply_L(f, p)
+    assert rel(R.apply_K(T(f, dtype)), O.apply_K(f, p)) <= TOL[dtype]["op"]
+    assert rel(R.apply_L(T(f, dtype)), Lf) <= l_tol(p, f, Lf, dtype)
+    s = T(f[1], dtype)
+    R.apply_K(s, out=s)
+    assert rel(s, O.apply_K(f[1], p)) <= TOL[dtype]["op"]
+    assert np.isfinite(float(s.double().sum()))
+
+
+def test_addend_of_the_run_time_inverse_pass():
+    """The adjoint sweep adds K's term on the inverse pass: gradient and Hv on a
+    grid without compile-time kernels."""
+    n, dtype = (20, 18, 42), torch.float64
+    R, p = make(n, dtype, nt=3)
+    I0, I1 = random_field(n, 3, components=1)[0], random_field(n, 4, components=1)[0]
+    v0, dv = 0.2 * random_field(n, 5), random_field(n, 6)
+    R.set_images(T(I0, dtype), T(I1, dtype))
+    lin = O.linearize(v0, I0, I1, p)
+    g, _ = R.gradient(T(v0, dtype))
+    assert rel(g, O.gradient(v0, I0, I1, p, lin)[0]) <= TOL[dtype]["grad"]
+    assert rel(R.hessvec(T(dv, dtype)), O.hessvec(dv, lin, p)) <= TOL[dtype]["hv"]
