@@ -9,6 +9,8 @@
 //   index_quot                     integer quotient by a float reciprocal
 //   row_lanes                      x2 neighbours inside a row of lanes of the
 //                                  row-vectorised stencils
+//   sl_tile, sl_tile_block         tiles of the semi-Lagrangian kernels and their LDS
+//                                  windows (sl_tile_wrap: periodic index of a window)
 //   sl_axis                        cell and weight of a displaced point along one
 //                                  axis for the semi-Lagrangian gathers
 //
@@ -159,6 +161,72 @@ LDI_HD void sl_axis(int i, T d, int n, int& a, int& b, T& t) {
   int j = (i + int(f)) % n;
   a = j < 0 ? j + n : j;
   b = a + 1 == n ? 0 : a + 1;
+}
+
+// Tiles of the semi-Lagrangian kernels: a workgroup of 256 lanes covers T0 x0 planes
+// of T1 x1 rows of T2 voxels (T1 T2 <= 256, T2 <= 64: an x2 row is cut into equal
+// chunks), lane l the column (l / T2, l % T2) of every plane.  Its LDS window is the
+// tile with one voxel more on every side, (T0 + 2) planes of (T1 + 2) rows of T2 + 2.
+// Blocks are ordered so that each XCD owns a slab of x1 tiles, as in FieldTiling.
+constexpr int kSlLanes = 256, kSlRow = 64;
+// most window elements per lane: (T1 + 2) (T2 + 2) <= 396
+constexpr int sl_window_loads(int T0) { return ((T0 + 2) * 396 + kSlLanes - 1) / kSlLanes; }
+
+struct SlTile {
+  int T0, T1, T2;
+  int TX, TY, slab;  // tiles along x2 and x1; slab as in FieldTiling
+  unsigned blocks;
+  int row, plane, count;  // elements of a window's row, plane and all of it
+  float inv_T2, inv_row, inv_plane;
+};
+
+inline SlTile sl_tile(int n0, int n1, int n2, int T0) {
+  SlTile t;
+  t.T0 = T0;
+  const int chunks = (n2 + kSlRow - 1) / kSlRow;
+  t.T2 = (n2 + chunks - 1) / chunks;
+  t.T1 = kSlLanes / t.T2 < n1 ? kSlLanes / t.T2 : n1;
+  t.TX = (n2 + t.T2 - 1) / t.T2;
+  t.TY = (n1 + t.T1 - 1) / t.T1;
+  const int s = (t.TY + 7) / 8;
+  t.slab = (t.TY >= 8 && 800 * s <= 115 * t.TY) ? s : 0;
+  t.blocks = unsigned(t.TX) * unsigned(t.slab ? 8 * t.slab : t.TY) * unsigned((n0 + T0 - 1) / T0);
+  t.row = t.T2 + 2;
+  t.plane = (t.T1 + 2) * t.row;
+  t.count = (T0 + 2) * t.plane;
+  t.inv_T2 = 1.0f / float(t.T2);
+  t.inv_row = 1.0f / float(t.row);
+  t.inv_plane = 1.0f / float(t.plane);
+  return t;
+}
+
+// First voxel of block b's tile; false for a block past its XCD's own slab.
+LDI_HD bool sl_tile_block(const SlTile& t, int b, int& i0, int& i1, int& i2) {
+  bool own = true;
+  int by, bz;
+  const int k = t.slab ? b >> 3 : b, r = k / t.TX, bx = k - r * t.TX;
+  if (t.slab) {
+    const int x = b & 7, lo = (x * t.TY) >> 3, rows = (((x + 1) * t.TY) >> 3) - lo;
+    bz = r / t.slab;
+    const int ry = r - bz * t.slab;
+    own = ry < rows;
+    by = lo + ry;
+  } else {
+    bz = r / t.TY;
+    by = r - bz * t.TY;
+  }
+  i0 = bz * t.T0;
+  i1 = by * t.T1;
+  i2 = bx * t.T2;
+  return own;
+}
+
+// Grid index of window index w (0 .. tile length + 1) of a tile that starts at i:
+// i + w - 1, periodic (an edge tile's window reaches at most one tile past n, and no
+// tile is longer than n).
+LDI_HD int sl_tile_wrap(int i, int w, int n) {
+  const int j = i + w - 1;
+  return j < 0 ? j + n : j >= n ? j - n : j;
 }
 
 // ---------------------------------------------------------------------------

@@ -474,7 +474,6 @@ class Engine {
     copy(v_cur, v0, 3 * N);
     if (store) traj_invalidate();
     if (want_energy) dot_dev(mu_cur, v0, 3, 2);
-    if (with_sl) launch_fill<T>(3 * N, T(0), u[0], st, &prof);
     for (int n = 0; n < P.nt; ++n) {
       T* ms = all ? tmus[n] : sms;
       T* vs = all ? tvs[n] : svs;
@@ -482,7 +481,7 @@ class Engine {
       if (!mu_next) mu_next = (mu_cur == sm[0]) ? sm[1] : sm[0];
       T* v_next = all ? tv[n + 1] : ((v_cur == sv[0]) ? sv[1] : sv[0]);
       heun_step(mu_cur, v_cur, ms, vs, mu_next, v_next);
-      if (with_sl) launch_sl_step<T>(g, u[n & 1], v_cur, v_next, u[(n + 1) & 1], dt, st, &prof);
+      if (with_sl) launch_sl_step<T>(g, n > 0 ? u[n & 1] : nullptr, v_cur, v_next, u[(n + 1) & 1], dt, st, &prof);
       mu_cur = mu_next;
       v_cur = v_next;
     }
@@ -1723,9 +1722,8 @@ class Engine {
     if (int rc = ensure_pde()) return rc;
     if (int rc = check_finite(v, (long long)pde_slices(stationary) * 3 * N, "v")) return rc;
     T* buf[2] = {P.nt % 2 == 0 ? u1 : pacc, P.nt % 2 == 0 ? pacc : u1};
-    launch_fill<T>(3 * N, T(0), buf[0], st, &prof);
     for (int n = 0; n < P.nt; ++n)
-      launch_sl_step<T>(g, buf[n & 1], slice(v, n, stationary), slice(v, n + 1, stationary), buf[(n + 1) & 1], dt,
+      launch_sl_step<T>(g, n > 0 ? buf[n & 1] : nullptr, slice(v, n, stationary), slice(v, n + 1, stationary), buf[(n + 1) & 1], dt,
                         st, &prof);
     return hip_status("pde_displacement");
   }

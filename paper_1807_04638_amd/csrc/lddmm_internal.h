@@ -217,7 +217,8 @@ void launch_jacobian_det(const Grid& g, const T* u, T* det, hipStream_t st, Prof
 // ---------------------------------------------------------------------------
 // Semi-Lagrangian transport - sl.hip
 // ---------------------------------------------------------------------------
-// u_new(x) = u_old(X) + (X - x), X = x - dt/2 (v_new(x) + v_old(x - dt v_new(x)))
+// u_new(x) = u_old(X) + (X - x), X = x - dt/2 (v_new(x) + v_old(x - dt v_new(x)));
+// u_old == nullptr: u_old = 0 (the first step)
 template <typename T>
 void launch_sl_step(const Grid& g, const T* u_old, const T* v_old, const T* v_new, T* u_new, double dt,
                     hipStream_t st, Profiler* prof);

@@ -91,7 +91,9 @@ __device__ __forceinline__ void load_pair(const float* __restrict__ f, int o, fl
 }
 
 // FP32 reads each x2 pair with one load (half the gathers); FP64 reads the
-// corners one by one (its 16-byte pairs measured slower than two loads).
+// corners one by one (its 16-byte pairs measured slower than two loads).  At the end
+// of a row the pair before it holds the lower corner, and only the upper one takes a
+// load of its own.
 template <typename T>
 __device__ __forceinline__ T tri_eval(const Tri<T>& tr, const T* __restrict__ f) {
   T acc = T(0);
@@ -99,10 +101,9 @@ __device__ __forceinline__ T tri_eval(const Tri<T>& tr, const T* __restrict__ f)
   for (int k = 0; k < 4; ++k) {
     T lo, hi;
     if constexpr (sizeof(T) == 4) {
-      if (!tr.wrap) {
-        load_pair(f, tr.o[k], lo, hi);
-      } else {
-        lo = f[tr.o[k]];
+      load_pair(f, tr.wrap ? tr.o[k] - 1 : tr.o[k], lo, hi);
+      if (tr.wrap) {
+        lo = hi;
         hi = f[tr.o[k] - tr.n2m1];
       }
     } else {
@@ -114,23 +115,193 @@ __device__ __forceinline__ T tri_eval(const Tri<T>& tr, const T* __restrict__ f)
   return acc;
 }
 
+// ---------------------------------------------------------------------------
+// One step along the characteristics: from the velocity vc at the voxel and vg
+// gathered at the predicted point, the foot (or head) of the characteristic, and
+// there the fields f[0 .. NF):
+//   P = +-dt vc,  disp = +-dt/2 (vc + vg(x + P)),  val_c = f_c(x + disp)
+// SL_START  u_new = disp                      (the shooting's first step, u = 0)
+// SL_STEP   u_new = u_old(X) + disp           (f = u_old)
+// SL_STATE  m_new = m_old(X)                  (PDE-LDDMM: the image itself)
+// SL_INCR   dm_new = dm_old(X) + dt/2 (s_old(X) + s_new(x))
+// SL_ADJOINT  lam_old = lam_new(Y) exp(dt/2 (D_old(x) + D_new(Y))), forward, D = div v
+//
+// Bound by the L1's return path when gathered from global memory (24 8-byte gathers
+// per voxel, texture data unit 98 % busy: 52 us at 128^3 FP32 for 100 MB).  A step
+// moves a point by less than a voxel as a rule, so the workgroup puts its tile of
+// each field with one voxel around it into the LDS (1.5 to 2.3 times the tile's
+// values, coalesced) and gathers there, without wrapping: 32 us.  A tile with a
+// longer displacement gathers from global memory.  The second fields' window is in
+// flight in registers while the first is gathered.
+// ---------------------------------------------------------------------------
+enum { SL_START, SL_STEP, SL_STATE, SL_INCR, SL_ADJOINT };
+
 template <typename T>
-__global__ void __launch_bounds__(256)
-    k_sl_step(SlGeo<T> g, const T* __restrict__ u_old, const T* __restrict__ v_old, const T* __restrict__ v_new,
-              T* __restrict__ u_new, T dt) {
-  int i0, i1, i2;
-  if (!tile_voxel(g.ft, g.n1, g.n2, i0, i1, i2)) return;
-  const int o = (i0 * g.n1 + i1) * g.n2 + i2;
-  T vn[3];
+struct SlIo {
+  const T* vc;
+  const T* vg;
+  const T* f[3];
+  const T* at_x;  // s_new (SL_INCR), D_old (SL_ADJOINT)
+  T* out;
+};
+
+// Window elements of a lane, NF fields: registers <- global, LDS <- registers.
+template <typename T, int NF, int NL>
+__device__ __forceinline__ void window_load(T (&r)[NF][NL], const T* const (&f)[3], const int (&go)[NL]) {
 #pragma unroll
-  for (int c = 0; c < 3; ++c) vn[c] = v_new[c * g.N + o];
-  const Tri<T> tp = tri_setup(g, i0, i1, i2, -dt * vn[0] * g.invh[0], -dt * vn[1] * g.invh[1], -dt * vn[2] * g.invh[2]);
-  T disp[3];
+  for (int c = 0; c < NF; ++c)
 #pragma unroll
-  for (int c = 0; c < 3; ++c) disp[c] = T(-0.5) * dt * (vn[c] + tri_eval(tp, v_old + c * g.N));
-  const Tri<T> tx = tri_setup(g, i0, i1, i2, disp[0] * g.invh[0], disp[1] * g.invh[1], disp[2] * g.invh[2]);
+    for (int l = 0; l < NL; ++l)
+      if (go[l] >= 0) r[c][l] = f[c][go[l]];
+}
+template <typename T, int NF, int NL>
+__device__ __forceinline__ void window_store(T* w, const T (&r)[NF][NL], const int (&go)[NL], int count) {
 #pragma unroll
-  for (int c = 0; c < 3; ++c) u_new[c * g.N + o] = tri_eval(tx, u_old + c * g.N) + disp[c];
+  for (int c = 0; c < NF; ++c)
+#pragma unroll
+    for (int l = 0; l < NL; ++l)
+      if (go[l] >= 0) w[c * count + int(threadIdx.x) + l * kSlLanes] = r[c][l];
+}
+
+// Cell and weights of a displacement of less than a voxel in a window: lower corner
+// relative to the voxel's own cell.
+template <typename T>
+struct WinTri {
+  int o;  // lower corner in the window
+  T t[3];
+};
+
+template <typename T>
+__device__ __forceinline__ bool win_setup(WinTri<T>& w, const T d[3], int centre, const SlTile& t) {
+  bool ok = true;
+  int f[3];
+#pragma unroll
+  for (int e = 0; e < 3; ++e) {
+    const T fl = floor(d[e]);
+    ok = ok && (fl == T(-1) || fl == T(0));
+    w.t[e] = d[e] - fl;
+    f[e] = fl < T(0) ? -1 : 0;
+  }
+  w.o = centre + f[0] * t.plane + f[1] * t.row + f[2];
+  return ok;
+}
+
+template <typename T>
+__device__ __forceinline__ T win_eval(const WinTri<T>& w, const T* win, const SlTile& t) {
+  T acc = T(0);
+#pragma unroll
+  for (int c0 = 0; c0 < 2; ++c0)
+#pragma unroll
+    for (int c1 = 0; c1 < 2; ++c1) {
+      const T* p = win + w.o + c0 * t.plane + c1 * t.row;
+      const T lo = p[0], hi = p[1];
+      const T w01 = (c0 ? w.t[0] : T(1) - w.t[0]) * (c1 ? w.t[1] : T(1) - w.t[1]);
+      acc += w01 * (lo + w.t[2] * (hi - lo));
+    }
+  return acc;
+}
+
+template <typename T, int KIND, int T0>
+__global__ void __launch_bounds__(kSlLanes) k_sl(SlGeo<T> g, SlTile t, SlIo<T> io, T dt) {
+  constexpr int NF = KIND == SL_START ? 0 : KIND == SL_STEP ? 3 : KIND == SL_STATE ? 1 : 2;
+  constexpr int NL = sl_window_loads(T0);
+  extern __shared__ __align__(16) unsigned char smem[];
+  T* win = reinterpret_cast<T*>(smem);
+  int b0, b1, b2;
+  if (!sl_tile_block(t, int(blockIdx.x), b0, b1, b2)) return;
+  const int lane = int(threadIdx.x);
+  int go[NL];  // grid offsets of the lane's window elements (-1: none)
+#pragma unroll
+  for (int l = 0; l < NL; ++l) {
+    const int e = lane + l * kSlLanes;
+    const int w0 = index_quot(e, t.inv_plane), r = e - mul24(w0, t.plane);
+    const int w1 = index_quot(r, t.inv_row), w2 = r - mul24(w1, t.row);
+    go[l] = e < t.count ? (sl_tile_wrap(b0, w0, g.n0) * g.n1 + sl_tile_wrap(b1, w1, g.n1)) * g.n2 +
+                              sl_tile_wrap(b2, w2, g.n2)
+                        : -1;
+  }
+  const T* const vg[3] = {io.vg, io.vg + g.N, io.vg + 2 * g.N};
+  T rv[3][NL];
+  window_load<T, 3, NL>(rv, vg, go);
+  const int l1 = index_quot(lane, t.inv_T2), l2 = lane - mul24(l1, t.T2);
+  const int i1 = b1 + l1, i2 = b2 + l2;
+  const bool column = l1 < t.T1 && i1 < g.n1 && i2 < g.n2;
+  const int s0 = g.n1 * g.n2, o0 = (b0 * g.n1 + i1) * g.n2 + i2;
+  const int centre = t.plane + (l1 + 1) * t.row + l2 + 1;
+  constexpr T sgn = KIND == SL_ADJOINT ? T(1) : T(-1);
+  T d[T0][3];  // vc, then the displacement
+  WinTri<T> w[T0];
+  bool near = true;
+#pragma unroll
+  for (int k = 0; k < T0; ++k) {
+    const bool on = column && b0 + k < g.n0;
+    T p[3];
+#pragma unroll
+    for (int c = 0; c < 3; ++c) {
+      d[k][c] = on ? io.vc[c * g.N + o0 + k * s0] : T(0);
+      p[c] = sgn * dt * d[k][c] * g.invh[c];
+    }
+    near = win_setup(w[k], p, centre + k * t.plane, t) && near;
+  }
+  window_store<T, 3, NL>(win, rv, go, t.count);
+  const bool near_p = !__syncthreads_or(!near);
+  constexpr int NR = NF > 0 ? NF : 1;
+  T rf[NR][NL];
+  if constexpr (NF > 0) window_load<T, NF, NL>(rf, io.f, go);
+  near = true;
+#pragma unroll
+  for (int k = 0; k < T0; ++k) {
+    const bool on = column && b0 + k < g.n0;
+    T v[3] = {T(0), T(0), T(0)};
+    if (near_p) {
+      if (column) {
+#pragma unroll
+        for (int c = 0; c < 3; ++c) v[c] = win_eval(w[k], win + c * t.count, t);
+      }
+    } else if (on) {
+      const Tri<T> tp = tri_setup(g, b0 + k, i1, i2, sgn * dt * d[k][0] * g.invh[0], sgn * dt * d[k][1] * g.invh[1],
+                                  sgn * dt * d[k][2] * g.invh[2]);
+#pragma unroll
+      for (int c = 0; c < 3; ++c) v[c] = tri_eval(tp, vg[c]);
+    }
+    T p[3];
+#pragma unroll
+    for (int c = 0; c < 3; ++c) {
+      d[k][c] = on ? sgn * T(0.5) * dt * (d[k][c] + v[c]) : T(0);
+      p[c] = d[k][c] * g.invh[c];
+    }
+    if constexpr (NF > 0) near = win_setup(w[k], p, centre + k * t.plane, t) && near;
+  }
+  bool near_x = true;
+  if constexpr (NF > 0) {
+    near_x = !__syncthreads_or(!near);  // and the first window has been read
+    window_store<T, NF, NL>(win, rf, go, t.count);
+    __syncthreads();
+  }
+#pragma unroll
+  for (int k = 0; k < T0; ++k) {
+    if (!(column && b0 + k < g.n0)) continue;
+    T v[NR] = {};
+    if (near_x) {
+#pragma unroll
+      for (int c = 0; c < NF; ++c) v[c] = win_eval(w[k], win + c * t.count, t);
+    } else {
+      const Tri<T> tx = tri_setup(g, b0 + k, i1, i2, d[k][0] * g.invh[0], d[k][1] * g.invh[1], d[k][2] * g.invh[2]);
+#pragma unroll
+      for (int c = 0; c < NF; ++c) v[c] = tri_eval(tx, io.f[c]);
+    }
+    const int o = o0 + k * s0;
+    if constexpr (KIND == SL_START || KIND == SL_STEP) {
+#pragma unroll
+      for (int c = 0; c < 3; ++c) io.out[c * g.N + o] = KIND == SL_STEP ? v[KIND == SL_STEP ? c : 0] + d[k][c] : d[k][c];
+    } else if constexpr (KIND == SL_STATE) {
+      io.out[o] = v[0];
+    } else if constexpr (KIND == SL_INCR) {
+      io.out[o] = v[0] + T(0.5) * dt * (v[NR - 1] + io.at_x[o]);
+    } else {
+      io.out[o] = v[0] * exp(T(0.5) * dt * (io.at_x[o] + v[NR - 1]));
+    }
+  }
 }
 
 template <typename T>
@@ -141,69 +312,6 @@ __global__ void __launch_bounds__(256)
   const int o = (i0 * g.n1 + i1) * g.n2 + i2;
   const Tri<T> t = tri_setup(g, i0, i1, i2, u[o] * g.invh[0], u[g.N + o] * g.invh[1], u[2 * g.N + o] * g.invh[2]);
   J[o] = tri_eval(t, I);
-}
-
-// ---------------------------------------------------------------------------
-// PDE-LDDMM (Section 2.3): the image itself transported by the state equation,
-// the adjoint (continuity) equation along forward characteristics, the
-// incremental state with its source term.
-// ---------------------------------------------------------------------------
-// m_new(x) = m_old(X), X = x - dt/2 (v_new(x) + v_old(x - dt v_new(x)))
-template <typename T>
-__global__ void __launch_bounds__(256)
-    k_pde_state(SlGeo<T> g, const T* __restrict__ m_old, const T* __restrict__ v_old, const T* __restrict__ v_new,
-                T* __restrict__ m_new, T dt) {
-  int i0, i1, i2;
-  if (!tile_voxel(g.ft, g.n1, g.n2, i0, i1, i2)) return;
-  const int o = (i0 * g.n1 + i1) * g.n2 + i2;
-  T vn[3];
-#pragma unroll
-  for (int c = 0; c < 3; ++c) vn[c] = v_new[c * g.N + o];
-  const Tri<T> tp = tri_setup(g, i0, i1, i2, -dt * vn[0] * g.invh[0], -dt * vn[1] * g.invh[1], -dt * vn[2] * g.invh[2]);
-  T disp[3];
-#pragma unroll
-  for (int c = 0; c < 3; ++c) disp[c] = T(-0.5) * dt * (vn[c] + tri_eval(tp, v_old + c * g.N));
-  const Tri<T> tx = tri_setup(g, i0, i1, i2, disp[0] * g.invh[0], disp[1] * g.invh[1], disp[2] * g.invh[2]);
-  m_new[o] = tri_eval(tx, m_old);
-}
-
-// dm_new(x) = dm_old(X) + dt/2 (s_old(X) + s_new(x)), X as in k_pde_state
-template <typename T>
-__global__ void __launch_bounds__(256)
-    k_pde_incr(SlGeo<T> g, const T* __restrict__ dm_old, const T* __restrict__ s_old, const T* __restrict__ s_new,
-               const T* __restrict__ v_old, const T* __restrict__ v_new, T* __restrict__ dm_new, T dt) {
-  int i0, i1, i2;
-  if (!tile_voxel(g.ft, g.n1, g.n2, i0, i1, i2)) return;
-  const int o = (i0 * g.n1 + i1) * g.n2 + i2;
-  T vn[3];
-#pragma unroll
-  for (int c = 0; c < 3; ++c) vn[c] = v_new[c * g.N + o];
-  const Tri<T> tp = tri_setup(g, i0, i1, i2, -dt * vn[0] * g.invh[0], -dt * vn[1] * g.invh[1], -dt * vn[2] * g.invh[2]);
-  T disp[3];
-#pragma unroll
-  for (int c = 0; c < 3; ++c) disp[c] = T(-0.5) * dt * (vn[c] + tri_eval(tp, v_old + c * g.N));
-  const Tri<T> tx = tri_setup(g, i0, i1, i2, disp[0] * g.invh[0], disp[1] * g.invh[1], disp[2] * g.invh[2]);
-  dm_new[o] = tri_eval(tx, dm_old) + T(0.5) * dt * (tri_eval(tx, s_old) + s_new[o]);
-}
-
-// lam_old(x) = lam_new(Y) exp(dt/2 (D_old(x) + D_new(Y))),
-// Y = x + dt/2 (v_old(x) + v_new(x + dt v_old(x))), D = div v
-template <typename T>
-__global__ void __launch_bounds__(256)
-    k_pde_adjoint(SlGeo<T> g, const T* __restrict__ lam_new, const T* __restrict__ D_old, const T* __restrict__ D_new,
-                  const T* __restrict__ v_old, const T* __restrict__ v_new, T* __restrict__ lam_old, T dt) {
-  int i0, i1, i2;
-  if (!tile_voxel(g.ft, g.n1, g.n2, i0, i1, i2)) return;
-  const int o = (i0 * g.n1 + i1) * g.n2 + i2;
-  T vo[3];
-#pragma unroll
-  for (int c = 0; c < 3; ++c) vo[c] = v_old[c * g.N + o];
-  const Tri<T> tp = tri_setup(g, i0, i1, i2, dt * vo[0] * g.invh[0], dt * vo[1] * g.invh[1], dt * vo[2] * g.invh[2]);
-  T disp[3];
-#pragma unroll
-  for (int c = 0; c < 3; ++c) disp[c] = T(0.5) * dt * (vo[c] + tri_eval(tp, v_new + c * g.N));
-  const Tri<T> ty = tri_setup(g, i0, i1, i2, disp[0] * g.invh[0], disp[1] * g.invh[1], disp[2] * g.invh[2]);
-  lam_old[o] = tri_eval(ty, lam_new) * exp(T(0.5) * dt * (D_old[o] + tri_eval(ty, D_new)));
 }
 
 // D = div_h v (central differences)
@@ -245,28 +353,51 @@ __global__ void __launch_bounds__(256)
 
 }  // namespace
 
+namespace {
+
+// Planes per tile: the more, the fewer window values per voxel (1.9, 2.3, 3.5 times
+// the tile's for 4, 2, 1 planes of 8 x 32 voxels); halved until at least 1024
+// workgroups share the 256 compute units.  us per sl_step with 4, 2, 1 planes: 128^3
+// FP32 31.9, 36.3, 39.9 (52 by gathers from global memory); 64^3 FP32 10.6, 8.9, 8.9
+// (10.2); 32^3 FP32 10.0, 7.5, 6.1 (9.2).  FP64 stops at 2 (128^3: 63, 54, 83; 80 by
+// gathers): four planes' registers leave two waves per SIMD.
+template <typename T, int KIND>
+void launch_sl(const char* name, const Grid& g, const SlIo<T>& io, double dt, hipStream_t st, Profiler* prof) {
+  KernelTimer timer(prof, name);
+  SlTile t = sl_tile(g.n0, g.n1, g.n2, sizeof(T) == 4 ? 4 : 2);
+  while (t.T0 > 1 && t.blocks < 1024) t = sl_tile(g.n0, g.n1, g.n2, t.T0 / 2);
+  const size_t lds = size_t(3) * t.count * sizeof(T);
+  const SlGeo<T> geo = make_sl_geo<T>(g);
+  if constexpr (sizeof(T) == 4)
+    if (t.T0 == 4) {
+      LDDMM_LAUNCH(timer.start, timer.stop, (k_sl<T, KIND, 4>), t.blocks, kSlLanes, lds, st, geo, t, io, T(dt));
+      return;
+    }
+  if (t.T0 == 2)
+    LDDMM_LAUNCH(timer.start, timer.stop, (k_sl<T, KIND, 2>), t.blocks, kSlLanes, lds, st, geo, t, io, T(dt));
+  else
+    LDDMM_LAUNCH(timer.start, timer.stop, (k_sl<T, KIND, 1>), t.blocks, kSlLanes, lds, st, geo, t, io, T(dt));
+}
+
+}  // namespace
+
 template <typename T>
 void launch_pde_state(const Grid& g, const T* m_old, const T* v_old, const T* v_new, T* m_new, double dt,
                       hipStream_t st, Profiler* prof) {
-  KernelTimer t(prof, "pde_state");
-  const FieldTiling ft = make_field_tiling(g);
-  LDDMM_LAUNCH(t.start, t.stop, k_pde_state<T>, ft.blocks, dim3(ft.BX, ft.BY), 0, st, make_sl_geo<T>(g), m_old, v_old, v_new, m_new, T(dt));
+  launch_sl<T, SL_STATE>("pde_state", g, {v_new, v_old, {m_old, nullptr, nullptr}, nullptr, m_new}, dt, st, prof);
 }
 
 template <typename T>
 void launch_pde_incr(const Grid& g, const T* dm_old, const T* s_old, const T* s_new, const T* v_old, const T* v_new,
                      T* dm_new, double dt, hipStream_t st, Profiler* prof) {
-  KernelTimer t(prof, "pde_incremental_state");
-  const FieldTiling ft = make_field_tiling(g);
-  LDDMM_LAUNCH(t.start, t.stop, k_pde_incr<T>, ft.blocks, dim3(ft.BX, ft.BY), 0, st, make_sl_geo<T>(g), dm_old, s_old, s_new, v_old, v_new, dm_new, T(dt));
+  launch_sl<T, SL_INCR>("pde_incremental_state", g, {v_new, v_old, {dm_old, s_old, nullptr}, s_new, dm_new}, dt, st,
+                        prof);
 }
 
 template <typename T>
 void launch_pde_adjoint(const Grid& g, const T* lam_new, const T* D_old, const T* D_new, const T* v_old,
                         const T* v_new, T* lam_old, double dt, hipStream_t st, Profiler* prof) {
-  KernelTimer t(prof, "pde_adjoint");
-  const FieldTiling ft = make_field_tiling(g);
-  LDDMM_LAUNCH(t.start, t.stop, k_pde_adjoint<T>, ft.blocks, dim3(ft.BX, ft.BY), 0, st, make_sl_geo<T>(g), lam_new, D_old, D_new, v_old, v_new, lam_old, T(dt));
+  launch_sl<T, SL_ADJOINT>("pde_adjoint", g, {v_old, v_new, {lam_new, D_new, nullptr}, D_old, lam_old}, dt, st, prof);
 }
 
 template <typename T>
@@ -294,9 +425,12 @@ void launch_pde_source(const Grid& g, const T* m, const T* dv, T* s, hipStream_t
 template <typename T>
 void launch_sl_step(const Grid& g, const T* u_old, const T* v_old, const T* v_new, T* u_new, double dt,
                     hipStream_t st, Profiler* prof) {
-  KernelTimer t(prof, "sl_step");
-  const FieldTiling ft = make_field_tiling(g);
-  LDDMM_LAUNCH(t.start, t.stop, k_sl_step<T>, ft.blocks, dim3(ft.BX, ft.BY), 0, st, make_sl_geo<T>(g), u_old, v_old, v_new, u_new, T(dt));
+  if (!u_old) {
+    launch_sl<T, SL_START>("sl_step", g, {v_new, v_old, {nullptr, nullptr, nullptr}, nullptr, u_new}, dt, st, prof);
+    return;
+  }
+  launch_sl<T, SL_STEP>("sl_step", g, {v_new, v_old, {u_old, u_old + g.N, u_old + 2 * g.N}, nullptr, u_new}, dt, st,
+                        prof);
 }
 
 template <typename T>
