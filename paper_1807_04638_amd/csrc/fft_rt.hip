@@ -354,13 +354,14 @@ __global__ void __launch_bounds__(1024, (rt_plane_waves(sizeof(T), BIG))) k_plan
 #undef LDDMM_RT_CALL
 }
 
-// 1 / x: the hardware's FP32 reciprocal (1 ulp) with one Newton step, which leaves
-// it within the rounding of the division it replaces; x >= 1 here.
-__device__ __forceinline__ float rt_recip(float x) {
-  const float r = __builtin_amdgcn_rcpf(x);
-  return fmaf(r, fmaf(-x, r, 1.0f), r);
+// a / x: the hardware's FP32 reciprocal (1 ulp) and one correction of the quotient,
+// which rounds as the division it replaces does (to half an ulp but for rare ties) at
+// a third of its instructions; x >= 1 here.
+__device__ __forceinline__ float rt_div(float a, float x) {
+  const float r = __builtin_amdgcn_rcpf(x), q = a * r;
+  return fmaf(fmaf(-x, q, a), r, q);
 }
-__device__ __forceinline__ double rt_recip(double x) { return 1.0 / x; }
+__device__ __forceinline__ double rt_div(double a, double x) { return a / x; }
 
 // The last DIF stage (stride 1), the symbol and the first DIT stage in registers.
 template <typename T, int R>
@@ -379,7 +380,7 @@ __device__ __forceinline__ void rt_symbol(cplx<T>* A, const T* ksq0, const T* ks
       const T bq = a.alpha * ksq0[u * R + i] + c12;
       T pw = bq * (a.s >= 2 ? bq : T(1));
       for (int k = 2; k < a.s; ++k) pw *= bq;
-      v[i] = c_scale(v[i], a.op == LDDMM_OP_K ? a.scale * rt_recip(pw) : a.scale * pw);
+      v[i] = c_scale(v[i], a.op == LDDMM_OP_K ? rt_div(a.scale, pw) : a.scale * pw);
     }
     Dft<T, R, +1>::run(v);
 #pragma unroll
