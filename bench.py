@@ -118,6 +118,7 @@ TUNED_KEYS = (
     "fft.fused",
     "fft.static_kernels",
     "stencil.rowvec",
+    "stencil.segments",
     "stencil.pair_rows",
 )
 KERNEL_SOURCES = {
@@ -165,7 +166,7 @@ def shape_keys(kernel):
         return ("fft.pencil_tb", "fft.pencil_threads", "fft.fused", "fft.static_kernels", "fft.plane_halves_used")
     if kernel.startswith("fft_"):
         return ("fft.plane_threads", "fft.rows_rb", "fft.fused", "fft.static_kernels", "fft.plane_halves_used")
-    return ("stencil.rowvec",)
+    return ("stencil.rowvec", "stencil.segments")
 
 
 def make_pair(spec, dtype, dev, torch, Registration, synth):

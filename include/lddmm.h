@@ -314,6 +314,12 @@ int lddmm_profile_read(lddmm_ctx* ctx, const char** names, int64_t* counts, doub
  *                                           the smallest valid width in FP64, the widest
  *                                           in FP32, 0 where none is valid; same
  *                                           operators, summed in another order
+ *   "stencil.segments"    0, 2, 4           voxels per lane of the same kernels with rows in
+ *                                           segments of 32 lanes (half a wave): rows of up to
+ *                                           32 lanes whole, longer ones cut, with a halo lane at
+ *                                           either end (2 only).  0: the form of
+ *                                           stencil.rowvec, whose setting clears this.
+ *                                           Default by grid and dtype; same operators
  *   "stencil.pair_rows"   0 | 1             with N2 / rowvec = 32 and N1 even a wave holds two
  *                                           x1 rows; 1: the row each half needs from the other
  *                                           comes by a lane swap instead of a load.  Default 1

@@ -43,6 +43,30 @@ struct FieldTiling {
   unsigned blocks; // TX * N0 * (8 slab, or TY in linear order)
 };
 
+// Host: tile rows of the largest slab when 8 XCDs share TY of them, 0 where that is
+// more than 15 % above the mean or there are fewer than 8.
+inline int slab_rows(int TY) {
+  const int s = (TY + 7) / 8;
+  return TY >= 8 && 800 * s <= 115 * TY ? s : 0;
+}
+
+// Host: x1 rows per block, `most` of them or the largest half, quarter, ... (at least
+// `least`) whose tile rows share evenly over the XCDs; linear order where none does.
+// 90 x 108 x 100 FP64, 50-lane rows: 27 tile rows of 4 in linear order 72 us a tangent
+// corrector, 54 of 2 in slabs 50 us.
+inline void tile_rows(FieldTiling& t, int n1, int most, int least) {
+  t.BY = most;
+  for (int by = most; by >= least; by /= 2)
+    if (slab_rows((n1 + by - 1) / by)) {
+      t.BY = by;
+      break;
+    } else if (by % 2 != 0) {
+      break;
+    }
+  t.TY = (n1 + t.BY - 1) / t.BY;
+  t.slab = slab_rows(t.TY);
+}
+
 // Host: the tiling of an n0 x n1 x n2 grid (n2 = row length in lanes for the
 // row-vectorised kernels).
 inline FieldTiling field_tiling(int n0, int n1, int n2) {
@@ -50,13 +74,8 @@ inline FieldTiling field_tiling(int n0, int n1, int n2) {
   int bx = (n2 + 31) / 32 * 32;
   if (bx > 256) bx = 256;
   t.BX = bx;
-  t.BY = 256 / bx > 0 ? 256 / bx : 1;
   t.TX = (n2 + t.BX - 1) / t.BX;
-  t.TY = (n1 + t.BY - 1) / t.BY;
-  // XCD-aware order where the largest slab is at most 15 % above the mean
-  // (uneven slabs make the XCDs with one more row finish last)
-  const int s = (t.TY + 7) / 8;
-  t.slab = (t.TY >= 8 && 800 * s <= 115 * t.TY) ? s : 0;
+  tile_rows(t, n1, 256 / bx > 0 ? 256 / bx : 1, bx % 64 == 0 ? 1 : 2);  // whole waves
   t.blocks = unsigned(t.TX) * unsigned(t.slab ? 8 * t.slab : t.TY) * unsigned(n0);
   return t;
 }
@@ -146,6 +165,69 @@ inline bool row_vector_valid(int n2, int vw) {
   return n2 % vw == 0 && n2 / vw >= 32 && n2 / vw <= 64;
 }
 
+// Rows in segments of 32 lanes (half a wave): a row of RW lanes is cut into `chunks`
+// of `out` lanes, each with a halo lane on either side that only holds the x2
+// neighbour of the first and last (RW <= 32: one chunk, the whole periodic row, no
+// halo).
+struct RowSegments {
+  int RW, chunks, out;
+};
+inline RowSegments row_segments(int RW) {
+  RowSegments r{RW, 1, RW};
+  if (RW > 32) {
+    r.chunks = (RW + 29) / 30;
+    r.out = (RW + r.chunks - 1) / r.chunks;
+  }
+  return r;
+}
+// Host: segments of vw voxels per lane for rows of n2 voxels: 2 or 4 where the row is
+// one segment, 2 where it is cut.
+inline bool row_segments_valid(int n2, int vw) {
+  return (vw == 2 || vw == 4) && n2 % vw == 0 && n2 / vw >= 4 && (vw == 2 || n2 / vw <= 32);
+}
+
+// Host: voxels per lane of the segments a grid takes by default (0: the rows of 32 to
+// 64 lanes of `rowvec`, or one voxel per thread).  A segment holds two x1 rows per
+// wave, so one x1 row in two comes by a lane swap, and a wide aligned access per lane;
+// it pays with its halo and spare lanes.  Sum over the six tangent, adjoint and EPDiff
+// stages in us, rows of 32 to 64 lanes / segments:
+//   FP32, one segment of width 4 against a row that is not 32 lanes: N2 = 72 119 / 81,
+//     84 153 / 111, 100 168 / 129, 112 226 / 167, 120 184 / 143 (96, 32 lanes of width
+//     3: 115 / 119; cut rows lose: 180 923 / 1099)
+//   FP64, one segment of width 2: 64^3 76 / 60, N2 = 50 68 / 54
+//   FP64, cut rows of width 2 against widths 3 (24 unaligned bytes) and 4: N2 = 140
+//     730 / 637, 160 765 / 657, 180 1970 / 1820 (head grid), 240 1022 / 932; against
+//     one voxel per thread: 210 1298 / 890.  Rows of 64 lanes stay (192 788 / 827,
+//     256 4640 / 4630), as do widths 2 up to N2 = 128 (112 264 / 284)
+//   FP32, cut rows against one voxel per thread, N1 even: 210 507 / 483
+inline int default_segments(int n1, int n2, bool fp64, int rowvec) {
+  const int lanes = rowvec ? n2 / rowvec : 0;
+  if (fp64) {
+    if (n2 % 2 != 0 || lanes == 64 && rowvec > 1) return 0;
+    return (n2 / 2 > 16 && n2 / 2 <= 32) || n2 > 128 ? 2 : 0;
+  }
+  if (lanes != 32 && n2 > 64 && n2 % 4 == 0 && n2 / 4 <= 32) return 4;
+  return !rowvec && n1 % 2 == 0 && n2 % 2 == 0 && n2 > 128 ? 2 : 0;
+}
+
+// Host: tiling in segments, up to 8 x1 rows per block.
+inline FieldTiling segment_tiling(int n0, int n1, const RowSegments& r) {
+  FieldTiling t;
+  t.BX = 32;
+  t.TX = r.chunks;
+  tile_rows(t, n1, 8, 2);
+  t.blocks = unsigned(t.TX) * unsigned(t.slab ? 8 * t.slab : t.TY) * unsigned(n0);
+  return t;
+}
+
+// Lane pos (0 .. 31) of chunk k of a cut row: the row lane it loads (periodic) and
+// whether it owns voxels.
+LDI_HD bool segment_lane(const RowSegments& r, int k, int pos, int& j) {
+  const int q = k * r.out + pos - 1;
+  j = q < 0 ? q + r.RW : q >= r.RW ? q - r.RW : q;
+  return pos >= 1 && pos <= r.out && q < r.RW;
+}
+
 // Semi-Lagrangian gather along one axis: grid index i displaced by d voxels.
 // Offsets beyond a million voxels (or NaN) are clamped first, so the integer
 // conversion cannot overflow and the periodic wrap keeps every index in
@@ -188,8 +270,7 @@ inline SlTile sl_tile(int n0, int n1, int n2, int T0) {
   t.T1 = kSlLanes / t.T2 < n1 ? kSlLanes / t.T2 : n1;
   t.TX = (n2 + t.T2 - 1) / t.T2;
   t.TY = (n1 + t.T1 - 1) / t.T1;
-  const int s = (t.TY + 7) / 8;
-  t.slab = (t.TY >= 8 && 800 * s <= 115 * t.TY) ? s : 0;
+  t.slab = slab_rows(t.TY);
   t.blocks = unsigned(t.TX) * unsigned(t.slab ? 8 * t.slab : t.TY) * unsigned((n0 + T0 - 1) / T0);
   t.row = t.T2 + 2;
   t.plane = (t.T1 + 2) * t.row;

@@ -218,6 +218,7 @@ class Engine {
         g.rowvec = vw;
         if (sizeof(T) == 8) break;
       }
+    g.segvec = default_segments(g.n1, g.n2, sizeof(T) == 8, g.rowvec);
     N = g.N;
     cell = g.h0 * g.h1 * g.h2;
     dt = 1.0 / p.nt;
@@ -849,15 +850,17 @@ class Engine {
     // Stencil kernels: one voxel per thread or VW voxels per lane, timed on the
     // tangent stage (the largest of them); work fields only, contents irrelevant.
     {
-      const int start_vw = g.rowvec, start_pair = g.pair_rows;
-      int best_vw = start_vw, best_pair = start_pair;
+      const int start_vw = g.rowvec, start_pair = g.pair_rows, start_seg = g.segvec;
+      int best_vw = start_vw, best_pair = start_pair, best_seg = start_seg;
       float best_t = -1.f, start_t = -1.f;
-      for (int vp : {0, 1, 2, 3, 4, 0x11, 0x12, 0x13, 0x14}) {
-        const int vw = vp & 0xf, pr = vp >> 4;
-        if (vw != 0 && !row_vector_valid(g.n2, vw)) continue;
-        if (pr && (vw == 0 || g.n2 / vw != 32 || g.n1 % 2 != 0)) continue;  // pairing needs 32-lane rows
+      // widths of rows of 32 to 64 lanes, unpaired and paired, then of segments (0x2.)
+      for (int vp : {0, 1, 2, 3, 4, 0x11, 0x12, 0x13, 0x14, 0x22, 0x24}) {
+        const int seg = vp >> 4 == 2 ? vp & 0xf : 0, vw = seg ? start_vw : vp & 0xf, pr = seg ? start_pair : vp >> 4;
+        if (seg ? !row_segments_valid(g.n2, seg) : vw != 0 && !row_vector_valid(g.n2, vw)) continue;
+        if (!seg && pr && (vw == 0 || g.n2 / vw != 32 || g.n1 % 2 != 0)) continue;  // pairing needs 32-lane rows
         g.rowvec = vw;
         g.pair_rows = pr;
+        g.segvec = seg;
         launch_tangent_stage<T>(g, X, Mu, W, Xs, Mus, X, Mu, Us, Whs, dt, 0.0, 1.0, st, nullptr);
         (void)hipEventRecord(a, st);
         for (int r = 0; r < reps; ++r)
@@ -871,12 +874,14 @@ class Engine {
           best_t = ms;
           best_vw = vw;
           best_pair = pr;
+          best_seg = seg;
         }
-        if (vw == start_vw && (pr == start_pair || vw == 0 || g.n2 / vw != 32)) start_t = ms;
+        if (seg == start_seg && vw == start_vw && (seg || pr == start_pair || vw == 0 || g.n2 / vw != 32)) start_t = ms;
       }
       const bool keep = start_t > 0.f && start_t <= 1.03f * best_t;
       g.rowvec = keep ? start_vw : best_vw;
       g.pair_rows = keep ? start_pair : best_pair;
+      g.segvec = keep ? start_seg : best_seg;
     }
     std::string msg;
     if (int rc = spectral_configure(sp, best, msg)) {
@@ -1389,6 +1394,14 @@ class Engine {
         return fail(LDDMM_EINVAL, "stencil.rowvec: N2 / value must be 32 to 64 with value 1, 2, 3 or 4");
       (void)hipStreamSynchronize(st);
       g.rowvec = int(value);
+      g.segvec = 0;
+      drop_graph();
+      return 0;
+    } else if (k == "stencil.segments") {
+      if (value != 0 && !row_segments_valid(g.n2, int(value)))
+        return fail(LDDMM_EINVAL, "stencil.segments: 0, 2, or 4 with N2 up to 128, dividing N2");
+      (void)hipStreamSynchronize(st);
+      g.segvec = int(value);
       drop_graph();
       return 0;
     } else if (k == "exec.branch_k") {
@@ -1457,6 +1470,8 @@ class Engine {
       *value = branch_k ? 1 : 0;
     else if (k == "stencil.rowvec")
       *value = g.rowvec;
+    else if (k == "stencil.segments")
+      *value = g.segvec;
     else
       return fail(LDDMM_EINVAL, "unknown option " + k);
     return 0;

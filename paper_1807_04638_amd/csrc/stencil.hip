@@ -16,12 +16,14 @@
 // The adjoint and Newton stages leave their K application out: they write K's
 // argument and the rest of the w update, and the inverse transform adds the K
 // term on its way out.
+#include <type_traits>
+
 #include "lddmm.h"
 #include "lddmm_internal.h"
 
 namespace lddmm {
 
-bool stencil_zero_start(const Grid& g) { return row_vector_valid(g.n2, g.rowvec); }
+bool stencil_zero_start(const Grid& g) { return g.segvec || row_vector_valid(g.n2, g.rowvec); }
 
 FieldTiling make_field_tiling(const Grid& g) { return field_tiling(g.n0, g.n1, g.n2); }
 
@@ -33,6 +35,7 @@ struct Geo {
   int N;  // voxels per component
   T inv2h[3];
   FieldTiling ft;
+  RowSegments seg;  // rows cut into 32-lane segments (the HALO kernels)
   int pair;  // launch the PAIR row-vectorised kernels: a wave holds two x1 rows (see VNbr)
 };
 
@@ -47,6 +50,7 @@ Geo<T> make_geo(const Grid& g) {
   o.inv2h[1] = T(0.5 / g.h1);
   o.inv2h[2] = T(0.5 / g.h2);
   o.ft = make_field_tiling(g);
+  o.seg = row_segments(g.n2);
   o.pair = 0;
   return o;
 }
@@ -445,12 +449,15 @@ struct VNbr {
   int ox[4];        // the same voxel at +x0, -x0, +x1, -x1
   int left, right;  // lanes holding the x2 neighbours
   bool upper;       // lanes 32-63 of a paired wave
+  bool out;         // the lane owns its voxels (HALO: false in halo and spare lanes)
 };
 
-template <typename T, int VW>
+template <typename T, int VW, bool HALO>
 __device__ __forceinline__ bool vvoxel(const Geo<T>& g, int RW, VNbr<VW>& nb) {
   int i0, i1, j;
-  if (!tile_voxel(g.ft, g.n1, g.n2 / VW, i0, i1, j)) return false;
+  if (!tile_voxel(g.ft, g.n1, HALO ? g.ft.TX * 32 : g.n2 / VW, i0, i1, j)) return false;
+  nb.out = true;
+  if (HALO) nb.out = segment_lane(g.seg, j >> 5, j & 31, j);
   const int i2 = j * VW;
   const int p0 = periodic_next(i0, g.n0), m0 = periodic_prev(i0, g.n0);
   const int p1 = periodic_next(i1, g.n1), m1 = periodic_prev(i1, g.n1);
@@ -462,7 +469,12 @@ __device__ __forceinline__ bool vvoxel(const Geo<T>& g, int RW, VNbr<VW>& nb) {
   nb.ox[2] = i0 * s0 + p1 * g.n2 + i2;
   nb.ox[3] = i0 * s0 + m1 * g.n2 + i2;
   const int lane = int(threadIdx.x + threadIdx.y * blockDim.x) & 63;
-  row_lanes(lane, RW, nb.left, nb.right);
+  if (HALO) {
+    nb.left = (lane & 32) + ((lane - 1) & 31);
+    nb.right = (lane & 32) + ((lane + 1) & 31);
+  } else {
+    row_lanes(lane, RW, nb.left, nb.right);
+  }
   nb.upper = lane >= 32;
   return true;
 }
@@ -613,12 +625,12 @@ __device__ __forceinline__ void vheun(T out[3][VW], const T* y0, T a0, int o, in
   }
 }
 
-template <typename T, int VW, bool PAIR>
+template <typename T, int VW, bool PAIR, bool HALO>
 __global__ void __launch_bounds__(256)
     k_epdiff_stage_v(Geo<T> g, int RW, const T* __restrict__ v, const T* __restrict__ mu, const T* mu0,
                      T* mu_out, T dt, T a0, T a1) {
   VNbr<VW> nb;
-  if (!vvoxel<T, VW>(g, RW, nb)) return;
+  if (!vvoxel<T, VW, HALO>(g, RW, nb)) return;
   T m[3][VW], vc[3][VW], a[3][VW] = {};
   vload3<T, VW>(m, mu, nb.o, g.N);
   vload3<T, VW>(vc, v, nb.o, g.N);
@@ -635,18 +647,18 @@ __global__ void __launch_bounds__(256)
 #pragma unroll
     for (int k = 0; k < VW; ++k) out[c][k] = a1 * (m[c][k] - dt * a[c][k]);
   vheun<T, VW>(out, mu0, a0, nb.o, g.N);
-  vstore3<T, VW>(mu_out, out, nb.o, g.N);
+  if (!HALO || nb.out) vstore3<T, VW>(mu_out, out, nb.o, g.N);
 }
 
 // ZS (the sweep's first step starts from X = 0): bit 1, the stage's X is zero
 // and not read (no ad_v X); bit 2, its start value X0 is zero and not read.
-template <typename T, int VW, bool PAIR, int ZS = 0>
+template <typename T, int VW, bool PAIR, bool HALO, int ZS = 0>
 __global__ void __launch_bounds__(256)
     k_tangent_stage_v(Geo<T> g, int RW, const T* __restrict__ X, const T* __restrict__ dmu, const T* __restrict__ W,
                       const T* __restrict__ v, const T* __restrict__ mu, const T* X0, const T* dmu0, T* X_out,
                       T* dmu_out, T dt, T a0, T a1, const T* __restrict__ Gf, T cf) {
   VNbr<VW> nb;
-  if (!vvoxel<T, VW>(g, RW, nb)) return;
+  if (!vvoxel<T, VW, HALO>(g, RW, nb)) return;
   T x[3][VW] = {}, vc[3][VW], dm[3][VW];
   if constexpr (!(ZS & 1)) vload3<T, VW>(x, X, nb.o, g.N);
   vload3<T, VW>(vc, v, nb.o, g.N);
@@ -693,21 +705,21 @@ __global__ void __launch_bounds__(256)
 #pragma unroll
       for (int c = 0; c < 3; ++c) xo[c][k] = sg * gv[c][k];
     }
-    vstore3<T, VW>(X_out, xo, nb.o, g.N);
+    if (!HALO || nb.out) vstore3<T, VW>(X_out, xo, nb.o, g.N);
     return;
   }
-  vstore3<T, VW>(X_out, xo, nb.o, g.N);
-  vstore3<T, VW>(dmu_out, mo, nb.o, g.N);
+  if (!HALO || nb.out) vstore3<T, VW>(X_out, xo, nb.o, g.N);
+  if (!HALO || nb.out) vstore3<T, VW>(dmu_out, mo, nb.o, g.N);
 }
 
 // ZS bit 2: the start value w0 is zero and not read (the sweep's first corrector).
-template <typename T, int VW, bool PAIR, int ZS = 0>
+template <typename T, int VW, bool PAIR, bool HALO, int ZS = 0>
 __global__ void __launch_bounds__(256)
     k_adjoint_stage_v(Geo<T> g, int RW, const T* __restrict__ U, const T* __restrict__ w, const T* __restrict__ mu,
                       const T* __restrict__ v, const T* U0, const T* w0, T* __restrict__ Z, T* __restrict__ Q,
                       T* U_out, T dt, T a0, T a1, const T* __restrict__ qadd, T qs) {
   VNbr<VW> nb;
-  if (!vvoxel<T, VW>(g, RW, nb)) return;
+  if (!vvoxel<T, VW, HALO>(g, RW, nb)) return;
   T u[3][VW], vc[3][VW], wc[3][VW], m[3][VW];
   vload3<T, VW>(u, U, nb.o, g.N);
   vload3<T, VW>(vc, v, nb.o, g.N);
@@ -744,19 +756,19 @@ __global__ void __launch_bounds__(256)
   if constexpr (!(ZS & 2)) vheun<T, VW>(q, w0, a0, nb.o, g.N);
   vheun<T, VW>(uo, U0, a0, nb.o, g.N);
   if (qadd) vheun<T, VW>(q, qadd, qs, nb.o, g.N);
-  vstore3<T, VW>(Z, z, nb.o, g.N);
-  vstore3<T, VW>(Q, q, nb.o, g.N);
-  vstore3<T, VW>(U_out, uo, nb.o, g.N);
+  if (!HALO || nb.out) vstore3<T, VW>(Z, z, nb.o, g.N);
+  if (!HALO || nb.out) vstore3<T, VW>(Q, q, nb.o, g.N);
+  if (!HALO || nb.out) vstore3<T, VW>(U_out, uo, nb.o, g.N);
 }
 
-template <typename T, int VW, bool PAIR>
+template <typename T, int VW, bool PAIR, bool HALO>
 __global__ void __launch_bounds__(256)
     k_newton_stage_v(Geo<T> g, int RW, const T* __restrict__ dU, const T* __restrict__ dw, const T* __restrict__ mu,
                      const T* __restrict__ w1, const T* __restrict__ dmu, const T* __restrict__ v,
                      const T* __restrict__ Wv, const T* __restrict__ U1, const T* dU0, const T* dw0,
                      T* __restrict__ Z, T* __restrict__ Q, T* dU_out, T dt, T a0, T a1) {
   VNbr<VW> nb;
-  if (!vvoxel<T, VW>(g, RW, nb)) return;
+  if (!vvoxel<T, VW, HALO>(g, RW, nb)) return;
   T du[3][VW], dwc[3][VW], m[3][VW], w1c[3][VW], dm[3][VW], vc[3][VW], wk[3][VW], u1[3][VW];
   vload3<T, VW>(du, dU, nb.o, g.N);
   vload3<T, VW>(dwc, dw, nb.o, g.N);
@@ -809,92 +821,70 @@ __global__ void __launch_bounds__(256)
     }
   vheun<T, VW>(uo, dU0, a0, nb.o, g.N);
   vheun<T, VW>(q, dw0, a0, nb.o, g.N);
-  vstore3<T, VW>(Z, z, nb.o, g.N);
-  vstore3<T, VW>(Q, q, nb.o, g.N);
-  vstore3<T, VW>(dU_out, uo, nb.o, g.N);
+  if (!HALO || nb.out) vstore3<T, VW>(Z, z, nb.o, g.N);
+  if (!HALO || nb.out) vstore3<T, VW>(Q, q, nb.o, g.N);
+  if (!HALO || nb.out) vstore3<T, VW>(dU_out, uo, nb.o, g.N);
 }
 
-// Lane width VW of the row-vectorised kernels for this grid (0: one voxel per thread).
-int row_vector_width(const Grid& g) { return row_vector_valid(g.n2, g.rowvec) ? g.rowvec : 0; }
-
+// Form of the row-vectorised kernels on a grid: voxels per lane (0: one voxel per
+// thread), lanes per row, and their geometry.
 template <typename T>
-Geo<T> make_vgeo(const Grid& g, int VW) {
-  Geo<T> o = make_geo<T>(g);
-  Grid gv = g;
-  gv.n2 = g.n2 / VW;
-  o.ft = make_field_tiling(gv);
+struct RowShape {
+  int VW = 0, RW = 0;
+  bool pair = false, halo = false;
+  Geo<T> geo;
+  dim3 grid, block;
+};
+
+// max_vw: kernels with more stencil fields take at most so many voxels per lane (to
+// keep their registers in bounds).
+template <typename T>
+RowShape<T> row_shape(const Grid& g, int max_vw = 4) {
+  RowShape<T> s;
+  if (g.segvec) {
+    s.VW = g.segvec <= max_vw ? g.segvec : max_vw;
+  } else if (row_vector_valid(g.n2, g.rowvec)) {
+    s.VW = g.rowvec <= max_vw ? g.rowvec : row_vector_valid(g.n2, max_vw) ? max_vw : 0;
+  }
+  if (!s.VW) return s;
+  s.RW = g.n2 / s.VW;
+  s.geo = make_geo<T>(g);
+  if (g.segvec) {
+    s.geo.seg = row_segments(s.RW);
+    s.halo = s.geo.seg.chunks > 1;
+    s.geo.ft = segment_tiling(g.n0, g.n1, s.geo.seg);
+  } else {
+    s.geo.ft = field_tiling(g.n0, g.n1, s.RW);
+  }
   // 32 lanes per row: a wave holds rows (i1, i1 + 1) with i1 even; with N1 even
   // both rows of every wave exist
-  o.pair = (g.n2 / VW == 32 && o.ft.BX == 32 && o.ft.BY % 2 == 0 && g.n1 % 2 == 0 && g.pair_rows) ? 1 : 0;
-  return o;
+  s.pair = s.geo.ft.BX == 32 && s.geo.ft.BY % 2 == 0 && g.n1 % 2 == 0 && g.pair_rows;
+  s.geo.pair = s.pair;
+  s.grid = dim3(s.geo.ft.blocks);
+  s.block = dim3(s.geo.ft.BX, s.geo.ft.BY);
+  return s;
 }
 
-#define LDDMM_ROWVEC_AT(kern, vw, pr, ...) \
-  LDDMM_LAUNCH(t.start, t.stop, kern<T LDDMM_COMMA vw LDDMM_COMMA pr>, grid_, block_, 0, st, gv, RW, __VA_ARGS__)
-// The same for kernels instantiated for VW = 1, 2 only.
-#define LDDMM_ROWVEC12(kern, ...)                                      \
-  do {                                                                 \
-    const Geo<T> gv = make_vgeo<T>(g, VW);                             \
-    const dim3 grid_(gv.ft.blocks), block_(gv.ft.BX, gv.ft.BY);        \
-    const int RW = g.n2 / VW;                                          \
-    if (VW == 1 && gv.pair)                                            \
-      LDDMM_ROWVEC_AT(kern, 1, true, __VA_ARGS__);                     \
-    else if (VW == 1)                                                  \
-      LDDMM_ROWVEC_AT(kern, 1, false, __VA_ARGS__);                    \
-    else if (gv.pair)                                                  \
-      LDDMM_ROWVEC_AT(kern, 2, true, __VA_ARGS__);                     \
-    else                                                               \
-      LDDMM_ROWVEC_AT(kern, 2, false, __VA_ARGS__);                    \
-  } while (0)
-#define LDDMM_ROWVEC(kern, ...)                                        \
-  do {                                                                 \
-    const Geo<T> gv = make_vgeo<T>(g, VW);                             \
-    const dim3 grid_(gv.ft.blocks), block_(gv.ft.BX, gv.ft.BY);        \
-    const int RW = g.n2 / VW;                                          \
-    if (VW == 1 && gv.pair)                                            \
-      LDDMM_ROWVEC_AT(kern, 1, true, __VA_ARGS__);                     \
-    else if (VW == 1)                                                  \
-      LDDMM_ROWVEC_AT(kern, 1, false, __VA_ARGS__);                    \
-    else if (VW == 2 && gv.pair)                                       \
-      LDDMM_ROWVEC_AT(kern, 2, true, __VA_ARGS__);                     \
-    else if (VW == 2)                                                  \
-      LDDMM_ROWVEC_AT(kern, 2, false, __VA_ARGS__);                    \
-    else if (VW == 3 && gv.pair)                                       \
-      LDDMM_ROWVEC_AT(kern, 3, true, __VA_ARGS__);                     \
-    else if (VW == 3)                                                  \
-      LDDMM_ROWVEC_AT(kern, 3, false, __VA_ARGS__);                    \
-    else if (gv.pair)                                                  \
-      LDDMM_ROWVEC_AT(kern, 4, true, __VA_ARGS__);                     \
-    else                                                               \
-      LDDMM_ROWVEC_AT(kern, 4, false, __VA_ARGS__);                    \
-  } while (0)
+template <int V>
+using Int = std::integral_constant<int, V>;
 
-// The same for the tangent and adjoint kernels with their zero-start variant ZS.
-#define LDDMM_ROWVEC_Z_AT(kern, vw, pr, z, ...)                                                       \
-  LDDMM_LAUNCH(t.start, t.stop, kern<T LDDMM_COMMA vw LDDMM_COMMA pr LDDMM_COMMA z>, grid_, block_, 0, st, gv, RW, \
-               __VA_ARGS__)
-#define LDDMM_ROWVEC_Z(kern, z, ...)                                   \
-  do {                                                                 \
-    const Geo<T> gv = make_vgeo<T>(g, VW);                             \
-    const dim3 grid_(gv.ft.blocks), block_(gv.ft.BX, gv.ft.BY);        \
-    const int RW = g.n2 / VW;                                          \
-    if (VW == 1 && gv.pair)                                            \
-      LDDMM_ROWVEC_Z_AT(kern, 1, true, z, __VA_ARGS__);                \
-    else if (VW == 1)                                                  \
-      LDDMM_ROWVEC_Z_AT(kern, 1, false, z, __VA_ARGS__);               \
-    else if (VW == 2 && gv.pair)                                       \
-      LDDMM_ROWVEC_Z_AT(kern, 2, true, z, __VA_ARGS__);                \
-    else if (VW == 2)                                                  \
-      LDDMM_ROWVEC_Z_AT(kern, 2, false, z, __VA_ARGS__);               \
-    else if (VW == 3 && gv.pair)                                       \
-      LDDMM_ROWVEC_Z_AT(kern, 3, true, z, __VA_ARGS__);                \
-    else if (VW == 3)                                                  \
-      LDDMM_ROWVEC_Z_AT(kern, 3, false, z, __VA_ARGS__);               \
-    else if (gv.pair)                                                  \
-      LDDMM_ROWVEC_Z_AT(kern, 4, true, z, __VA_ARGS__);                \
-    else                                                               \
-      LDDMM_ROWVEC_Z_AT(kern, 4, false, z, __VA_ARGS__);               \
-  } while (0)
+// f(VW, PAIR, HALO) as compile-time constants; widths above MAX are not instantiated.
+template <int MAX, typename T, class F>
+void with_row_shape(const RowShape<T>& s, F f) {
+  auto pair = [&](auto vw, auto halo) {
+    if (s.pair)
+      f(vw, std::true_type(), halo);
+    else
+      f(vw, std::false_type(), halo);
+  };
+  if (s.halo) return pair(Int<2>(), std::true_type());  // cut rows: width 2
+  if (s.VW == 1) return pair(Int<1>(), std::false_type());
+  if (s.VW == 2) return pair(Int<2>(), std::false_type());
+  if constexpr (MAX >= 4) {
+    if (s.VW == 3) return pair(Int<3>(), std::false_type());
+    return pair(Int<4>(), std::false_type());
+  }
+}
 
 dim3 ft_grid(const Grid& g) { return dim3(make_field_tiling(g).blocks); }
 dim3 ft_block(const Grid& g) {
@@ -913,8 +903,11 @@ template <typename T>
 void launch_epdiff_stage(const Grid& g, const T* v, const T* mu, const T* mu0, T* mu_out, double dt, double a0,
                          double a1, hipStream_t st, Profiler* prof) {
   KernelTimer t(prof, a0 != 0.0 ? "epdiff_stage_corr" : "epdiff_stage_pred");
-  if (const int VW = row_vector_width(g)) {
-    LDDMM_ROWVEC(k_epdiff_stage_v, v, mu, mu0 ? mu0 : mu, mu_out, T(dt), T(a0), T(a1));
+  const RowShape<T> s = row_shape<T>(g);
+  if (s.VW) {
+    with_row_shape<4>(s, [&](auto vw, auto pair, auto halo) {
+      LDDMM_LAUNCH(t.start, t.stop, (k_epdiff_stage_v<T, vw, pair, halo>), s.grid, s.block, 0, st, s.geo, s.RW, v, mu, mu0 ? mu0 : mu, mu_out, T(dt), T(a0), T(a1));
+    });
     return;
   }
   LDDMM_LAUNCH(t.start, t.stop, k_epdiff_stage<T>, ft_grid(g), ft_block(g), 0, st, make_geo<T>(g), v, mu, mu0 ? mu0 : mu, mu_out, T(dt), T(a0), T(a1));
@@ -924,19 +917,22 @@ template <typename T>
 void launch_tangent_stage(const Grid& g, const T* X, const T* dmu, const T* W, const T* v, const T* mu,
                           const T* X0, const T* dmu0, T* X_out, T* dmu_out, double dt, double a0, double a1,
                           hipStream_t st, Profiler* prof, const T* Gfin, double cfin, int zero) {
-  const bool zs = zero != 0 && row_vector_width(g) != 0;  // the zero-start variant runs
+  const RowShape<T> s = row_shape<T>(g);
+  const bool zs = zero != 0 && s.VW;  // the zero-start variant runs
   KernelTimer t(prof, a0 != 0.0 ? (zs ? "tangent_stage_corr_first" : "tangent_stage_corr")
                                 : (zs ? "tangent_stage_pred_first" : "tangent_stage_pred"));
-  if (const int VW = row_vector_width(g)) {
-    if (zero == 1)
-      LDDMM_ROWVEC_Z(k_tangent_stage_v, 1, X, dmu, W, v, mu, X0 ? X0 : X, dmu0 ? dmu0 : dmu, X_out, dmu_out, T(dt),
-                     T(a0), T(a1), Gfin, T(cfin));
-    else if (zero == 2)
-      LDDMM_ROWVEC_Z(k_tangent_stage_v, 2, X, dmu, W, v, mu, X0 ? X0 : X, dmu0 ? dmu0 : dmu, X_out, dmu_out, T(dt),
-                     T(a0), T(a1), Gfin, T(cfin));
-    else
-      LDDMM_ROWVEC_Z(k_tangent_stage_v, 0, X, dmu, W, v, mu, X0 ? X0 : X, dmu0 ? dmu0 : dmu, X_out, dmu_out, T(dt),
-                     T(a0), T(a1), Gfin, T(cfin));
+  if (s.VW) {
+    with_row_shape<4>(s, [&](auto vw, auto pair, auto halo) {
+      auto launch = [&](auto z) {
+        LDDMM_LAUNCH(t.start, t.stop, (k_tangent_stage_v<T, vw, pair, halo, z>), s.grid, s.block, 0, st, s.geo, s.RW, X, dmu, W, v, mu, X0 ? X0 : X, dmu0 ? dmu0 : dmu, X_out, dmu_out, T(dt), T(a0), T(a1), Gfin, T(cfin));
+      };
+      if (zero == 1)
+        launch(Int<1>());
+      else if (zero == 2)
+        launch(Int<2>());
+      else
+        launch(Int<0>());
+    });
     return;
   }
   LDDMM_LAUNCH(t.start, t.stop, k_tangent_stage<T>, ft_grid(g), ft_block(g), 0, st, make_geo<T>(g), X, dmu, W, v, mu, X0 ? X0 : X, dmu0 ? dmu0 : dmu, X_out, dmu_out, T(dt), T(a0), T(a1), Gfin, T(cfin));
@@ -946,15 +942,19 @@ template <typename T>
 void launch_adjoint_stage(const Grid& g, const T* U, const T* w, const T* mu, const T* v, const T* U0, const T* w0,
                           T* Z, T* Q, T* U_out, double dt, double a0, double a1, hipStream_t st, Profiler* prof,
                           const T* qadd, double qs, int zero) {
-  const bool zs = zero != 0 && row_vector_width(g) != 0;  // the zero-start variant runs
+  const RowShape<T> s = row_shape<T>(g);
+  const bool zs = zero != 0 && s.VW;  // the zero-start variant runs
   KernelTimer t(prof, a0 != 0.0 ? (zs ? "adjoint_stage_corr_first" : "adjoint_stage_corr") : "adjoint_stage_pred");
-  if (const int VW = row_vector_width(g)) {
-    if (zero == 2)
-      LDDMM_ROWVEC_Z(k_adjoint_stage_v, 2, U, w, mu, v, U0 ? U0 : U, w0 ? w0 : w, Z, Q, U_out, T(dt), T(a0), T(a1),
-                     qadd, T(qs));
-    else
-      LDDMM_ROWVEC_Z(k_adjoint_stage_v, 0, U, w, mu, v, U0 ? U0 : U, w0 ? w0 : w, Z, Q, U_out, T(dt), T(a0), T(a1),
-                     qadd, T(qs));
+  if (s.VW) {
+    with_row_shape<4>(s, [&](auto vw, auto pair, auto halo) {
+      auto launch = [&](auto z) {
+        LDDMM_LAUNCH(t.start, t.stop, (k_adjoint_stage_v<T, vw, pair, halo, z>), s.grid, s.block, 0, st, s.geo, s.RW, U, w, mu, v, U0 ? U0 : U, w0 ? w0 : w, Z, Q, U_out, T(dt), T(a0), T(a1), qadd, T(qs));
+      };
+      if (zero == 2)
+        launch(Int<2>());
+      else
+        launch(Int<0>());
+    });
     return;
   }
   LDDMM_LAUNCH(t.start, t.stop, k_adjoint_stage<T>, ft_grid(g), ft_block(g), 0, st, make_geo<T>(g), U, w, mu, v, U0 ? U0 : U, w0 ? w0 : w, Z, Q, U_out, T(dt), T(a0), T(a1), qadd, T(qs));
@@ -984,12 +984,11 @@ void launch_newton_stage(const Grid& g, const T* dU, const T* dw, const T* mu, c
                          const T* Wv, const T* U1, const T* dU0, const T* dw0, T* Z, T* Q, T* dU_out, double dt,
                          double a0, double a1, hipStream_t st, Profiler* prof) {
   KernelTimer t(prof, a0 != 0.0 ? "newton_stage_corr" : "newton_stage_pred");
-  // eight stencil fields: at most two voxels per lane keeps the registers in bounds
-  int VW = row_vector_width(g);
-  if (VW > 2) VW = row_vector_valid(g.n2, 2) ? 2 : 0;
-  if (VW) {
-    LDDMM_ROWVEC12(k_newton_stage_v, dU, dw, mu, w1, dmu, v, Wv, U1, dU0 ? dU0 : dU, dw0 ? dw0 : dw, Z, Q, dU_out,
-                   T(dt), T(a0), T(a1));
+  const RowShape<T> s = row_shape<T>(g, 2);  // eight stencil fields
+  if (s.VW) {
+    with_row_shape<2>(s, [&](auto vw, auto pair, auto halo) {
+      LDDMM_LAUNCH(t.start, t.stop, (k_newton_stage_v<T, vw, pair, halo>), s.grid, s.block, 0, st, s.geo, s.RW, dU, dw, mu, w1, dmu, v, Wv, U1, dU0 ? dU0 : dU, dw0 ? dw0 : dw, Z, Q, dU_out, T(dt), T(a0), T(a1));
+    });
     return;
   }
   LDDMM_LAUNCH(t.start, t.stop, k_newton_stage<T>, ft_grid(g), ft_block(g), 0, st, make_geo<T>(g), dU, dw, mu, w1, dmu, v, Wv, U1, dU0 ? dU0 : dU, dw0 ? dw0 : dw, Z, Q, dU_out, T(dt), T(a0), T(a1));

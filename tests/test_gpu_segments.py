@@ -1,0 +1,56 @@
+"""Stage kernels with x2 rows in 32-lane segments (whole and cut rows, N1 even and odd,
+1 to several tile rows per XCD) against the oracle: shooting, gradient, Gauss-Newton
+and Newton products, the tolerances of the other parity tests."""
+
+import pytest
+import torch
+
+import oracle as O
+from paper_1807_04638_amd import LddmmError
+from synth import random_field, random_velocity
+from test_gpu_parity import DTYPES, TOL, T, images, make, rel, say
+
+pytestmark = pytest.mark.gpu
+
+
+GRIDS = [((6, 8, 64), 2), ((5, 7, 36), 2), ((6, 8, 72), 4), ((4, 16, 128), 4), ((6, 8, 70), 2), ((5, 9, 126), 2),
+         ((4, 100, 60), 2), ((4, 6, 16), 4), ((6, 8, 180), 2)]
+# the flow on these two grows the velocity 44 and 5 times in unit time: with any form of
+# the stage kernels FP32 is 6e-5 and 1e-4 off, so they are held to the FP64 bounds only
+FP64_GRIDS = [((4, 6, 180), 2), ((4, 7, 250), 2)]
+
+
+@pytest.mark.parametrize("n, seg, dtype", [(n, s, d) for d in DTYPES for n, s in GRIDS]
+                         + [(n, s, torch.float64) for n, s in FP64_GRIDS])
+def test_segments(n, seg, dtype):
+    I0, I1 = images(n)
+    v0 = random_velocity(n, 2003, 0.5, kc=2.0)
+    dv = random_field(n, 6, kc=3.0)
+    p = O.Params(tuple(n), 0.01, 2, 3, 0.05)
+    tr = O.shoot(v0, p, I0)
+    go, lin = O.gradient(v0, I0, I1, p)
+    R, _ = make(n, dtype, nt=3, sigma2=0.05)
+    R.set_option("stencil.segments", seg)
+    assert R.get_option("stencil.segments") == seg
+    R.set_images(T(I0, dtype), T(I1, dtype))
+    out = R.shoot(T(v0, dtype))
+    g, _ = R.gradient(T(v0, dtype))
+    errs = dict(v1=rel(out["v1"], tr.v[-1]), grad=rel(g, go), hv=rel(R.hessvec(T(dv, dtype)), O.hessvec(dv, lin, p)),
+                hv_newton=rel(R.hessvec(T(dv, dtype), newton=True), O.hessvec_newton(dv, lin, p)))
+    say(f"  segments={seg}", {k: f"{e:.2e}" for k, e in errs.items()})
+    assert errs["v1"] <= TOL[dtype]["shoot"] and errs["grad"] <= TOL[dtype]["grad"]
+    assert errs["hv"] <= TOL[dtype]["hv"] and errs["hv_newton"] <= TOL[dtype]["hv"]
+
+
+def test_default_and_refused_widths():
+    R, _ = make((4, 6, 100), torch.float32, nt=1)
+    assert R.get_option("stencil.segments") == 4  # 25 lanes in one segment
+    for bad in (1, 3, 5, -2):
+        with pytest.raises(LddmmError):
+            R.set_option("stencil.segments", bad)
+    R.set_option("stencil.rowvec", 2)  # selecting a width of the other form clears it
+    assert R.get_option("stencil.segments") == 0
+    R, _ = make((4, 6, 180), torch.float64, nt=1)
+    assert R.get_option("stencil.segments") == 2
+    with pytest.raises(LddmmError):
+        R.set_option("stencil.segments", 4)  # cut rows take width 2 only
