@@ -56,6 +56,11 @@ __device__ void lds_fft(cplx<T>* buf, const FftPlan& pl, int count, int es, int 
       LDDMM_FFT_STAGE(5)
       LDDMM_FFT_STAGE(7)
       LDDMM_FFT_STAGE(9)
+      LDDMM_FFT_STAGE(6)
+      LDDMM_FFT_STAGE(10)
+      LDDMM_FFT_STAGE(12)
+      LDDMM_FFT_STAGE(14)
+      LDDMM_FFT_STAGE(15)
       default:
         break;
     }
@@ -1200,7 +1205,7 @@ int spectral_configure(SpectralPlan<T>& sp, const FftTuning& tune, std::string& 
       nstatic++;
     } else {
       plane_rt = true;
-      const bool big = has_radix16(xs > 1 ? sp.p1u : sp.p1) || has_radix16(sp.p2);
+      const bool big = has_big_radix(xs > 1 ? sp.p1u : sp.p1) || has_big_radix(sp.p2);
       k[KF_PLANE_FWD] = (void*)rt_plane_fwd<T>(big);
       k[KF_PLANE_INV] = k[KF_PLANE_INV_ADD] = (void*)rt_plane_inv<T>(big);
       // an odd row stride (LDS banks) where it fits
@@ -1214,7 +1219,7 @@ int spectral_configure(SpectralPlan<T>& sp, const FftTuning& tune, std::string& 
     nstatic++;
   } else {
     pencil_rt = true;
-    k[KF_PENCIL0] = (void*)rt_pencil<T>(xs, has_radix16(sp.p0));
+    k[KF_PENCIL0] = (void*)rt_pencil<T>(xs, has_big_radix(sp.p0));
   }
   // groups of xs sequences per pencil workgroup; the pencils also keep a symbol
   // term per sequence
@@ -1366,6 +1371,27 @@ int spectral_plan_tables(SpectralPlan<T>& sp, const int n[3], size_t max_lds, bo
     return LDDMM_EUNSUPPORTED;
   }
   const int H = sp.H, M = sp.M;
+  sp.xs = units ? plane_units<T>(n[1], H, max_lds) : 1;
+  if (sp.xs > 1 && !make_plan(n[1] / sp.xs, sp.p1u)) sp.xs = 1;
+  // Axes that no compile-time kernel transforms take the run-time kernels' plans of
+  // the fewest stages: one exchange through the LDS and one barrier less where 2 5 5
+  // becomes 5 10 or 8 2 3 becomes 6 8 (K at 100 x 96 x 100 FP32 46.5 -> 40.2 us, 128 x
+  // 120 x 140 FP64 98 -> 88, 180 x 210 x 180 FP32 154 -> 143).  Radices 12 to 16 only
+  // for planes whose units leave room for one workgroup per compute unit (180 x 210 x
+  // 180 FP64 planes 118 + 108 -> 113 + 99 us); with two (FP32, 76 KB) their registers
+  // cost the second one (52 + 51 -> 65 + 64), and the pencils, which transform a pair
+  // at a time, would spill (144 points FP32 17.5 -> 25.3).
+  void* f[3] = {nullptr, nullptr, nullptr};
+  if (sp.xs == 2) plane_static_halves<T, 512>(sp.p2, sp.p1u, f[0], f[1], f[2]);
+  if (!f[0]) plane_static<T, 512, false>(sp.p2, sp.p1, f[0], f[1], f[2]);
+  const bool fused = sp.xs > 1 || size_t(n[1]) * (M + 1) * sizeof(cplx<T>) <= max_lds;
+  if (!f[0] && fused) {
+    const bool big = size_t(n[1] / sp.xs) * M * sizeof(cplx<T>) > 80 * 1024;
+    make_wide_plan(H, big, sp.p2);
+    make_wide_plan(n[1], big, sp.p1);
+    if (sp.xs > 1) make_wide_plan(n[1] / sp.xs, big, sp.p1u);
+  }
+  if (!pencil_static<T, 2>(sp.p0, 16)) make_wide_plan(n[0], false, sp.p0);
   for (int i = 0; i < 12; ++i) off[i] = size_t(-1);
   off[0] = blob.put(twiddles<T>(n[0], n[0]));
   off[1] = blob.put(twiddles<T>(n[1], n[1]));
@@ -1388,8 +1414,6 @@ int spectral_plan_tables(SpectralPlan<T>& sp, const int n[3], size_t max_lds, bo
   off[7] = blob.put(k2);
   // unit tables: the x1 transform of length n1 / xs, the merge twiddles W_{n1}^{k1}
   // and |k1 + p n1 / xs|^2, p < xs, per slot of the unit transform
-  sp.xs = units ? plane_units<T>(n[1], H, max_lds) : 1;
-  if (sp.xs > 1 && !make_plan(n[1] / sp.xs, sp.p1u)) sp.xs = 1;
   if (sp.xs > 1) {
     const int u1 = n[1] / sp.xs;
     off[8] = blob.put(twiddles<T>(u1, u1));

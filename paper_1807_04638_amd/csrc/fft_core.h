@@ -1,4 +1,4 @@
-// fft_core.h - mixed-radix in-place FFT building blocks (radix 2, 3, 4, 5, 7, 8, 9, 16).
+// fft_core.h - mixed-radix in-place FFT building blocks (radix 2 to 10, 12, 14, 15, 16).
 //
 // The spectral operators L = (Id - alpha Laplacian)^s and K = L^-1 (Section 2.1
 // of the paper) are applied as forward FFT -> real symbol -> inverse FFT.  Since
@@ -239,6 +239,50 @@ struct Dft<T, 9, DIR> {
   }
 };
 
+// N = A B with A, B coprime by the prime-factor algorithm (Good's index maps): x at
+// (B n1 + A n2) mod N, B transforms of length A over n1, A of length B over n2, the
+// result with remainders (k1, k2) modulo (A, B) at frequency k.  No twiddles.
+template <typename T, int A, int B, int DIR>
+struct DftCoprime {
+  static constexpr int N = A * B;
+  static LD_HD constexpr int crt(int k1, int k2) {
+    int k = k1;
+    while (k % B != k2) k += A;
+    return k;
+  }
+  static LD_HD void run(cplx<T>* a) {
+    cplx<T> y[B][A];
+#pragma unroll
+    for (int n2 = 0; n2 < B; ++n2) {
+      cplx<T> g[A];
+#pragma unroll
+      for (int n1 = 0; n1 < A; ++n1) g[n1] = a[(B * n1 + A * n2) % N];
+      Dft<T, A, DIR>::run(g);
+#pragma unroll
+      for (int k1 = 0; k1 < A; ++k1) y[n2][k1] = g[k1];
+    }
+#pragma unroll
+    for (int k1 = 0; k1 < A; ++k1) {
+      cplx<T> h[B];
+#pragma unroll
+      for (int n2 = 0; n2 < B; ++n2) h[n2] = y[n2][k1];
+      Dft<T, B, DIR>::run(h);
+#pragma unroll
+      for (int k2 = 0; k2 < B; ++k2) a[crt(k1, k2)] = h[k2];
+    }
+  }
+};
+template <typename T, int DIR>
+struct Dft<T, 6, DIR> : DftCoprime<T, 2, 3, DIR> {};
+template <typename T, int DIR>
+struct Dft<T, 10, DIR> : DftCoprime<T, 2, 5, DIR> {};
+template <typename T, int DIR>
+struct Dft<T, 12, DIR> : DftCoprime<T, 4, 3, DIR> {};
+template <typename T, int DIR>
+struct Dft<T, 14, DIR> : DftCoprime<T, 2, 7, DIR> {};
+template <typename T, int DIR>
+struct Dft<T, 15, DIR> : DftCoprime<T, 3, 5, DIR> {};
+
 // Twiddle powers w[q] = W^(j q), q = 1..R-1, from one table read W^j (the
 // rest by complex products in registers: fewer LDS reads, a few ulp of error).
 template <typename T, int R>
@@ -257,11 +301,33 @@ LD_HD void twiddle_powers(cplx<T>* w, int j, int twstep, const cplx<T>* tw) {
   }
 }
 
+// The same with W^j, W^2j, W^4j and W^8j read from the table (j q twstep < n, so no
+// index wraps) and at most two products for each of the others. The run-time kernels use
+// it: with their larger radices the chain of products would round up to four times, the
+// same way in every row. FP32 K over 23 grids of odd and even lengths: geometric mean of
+// the error against 64 bits 2.62e-7, with the chain 3.01e-7, at the same time.
+template <typename T, int R>
+LD_HD void twiddle_reads(cplx<T>* w, int j, int twstep, const cplx<T>* tw) {
+  const int s = j * twstep;
+  w[1] = tw[s];
+  if (R > 2) w[2] = tw[2 * s];
+  if (R > 3) w[3] = c_mul(w[2], w[1]);
+  if (R > 4) w[4] = tw[4 * s];
+  if (R > 5) w[5] = c_mul(w[4], w[1]);
+  if (R > 6) w[6] = c_mul(w[4], w[2]);
+  if (R > 7) w[7] = c_mul(w[4], w[3]);
+  if (R > 8) {
+    w[8] = tw[8 * s];
+#pragma unroll
+    for (int q = 9; q < R; ++q) w[q] = c_mul(w[8], w[q - 8]);
+  }
+}
+
 // One butterfly of DIF stage with sub-length L = R * stride.  Elements at
 // base + t * step (t < R); j = position inside the sub-block; tw[m] =
 // exp(-2 pi i m / n); twstep = n / L.  TW = false when the stride is 1 (the
 // last DIF stage), where every twiddle is W^0 = 1.
-template <typename T, int R, bool TW = true>
+template <typename T, int R, bool TW = true, bool READ = false>
 LD_HD void dif_butterfly(cplx<T>* buf, int base, int step, int j, int twstep, const cplx<T>* tw) {
   cplx<T> a[R];
 #pragma unroll
@@ -270,7 +336,10 @@ LD_HD void dif_butterfly(cplx<T>* buf, int base, int step, int j, int twstep, co
   if constexpr (TW) {
     buf[base] = a[0];
     cplx<T> w[R];
-    twiddle_powers<T, R>(w, j, twstep, tw);
+    if constexpr (READ)
+      twiddle_reads<T, R>(w, j, twstep, tw);
+    else
+      twiddle_powers<T, R>(w, j, twstep, tw);
 #pragma unroll
     for (int q = 1; q < R; ++q) buf[base + q * step] = c_mul(a[q], w[q]);
   } else {
@@ -280,13 +349,16 @@ LD_HD void dif_butterfly(cplx<T>* buf, int base, int step, int j, int twstep, co
 }
 
 // Inverse of dif_butterfly up to the factor R (conjugate twiddle, then DFT).
-template <typename T, int R, bool TW = true>
+template <typename T, int R, bool TW = true, bool READ = false>
 LD_HD void dit_butterfly(cplx<T>* buf, int base, int step, int j, int twstep, const cplx<T>* tw) {
   cplx<T> a[R];
   if constexpr (TW) {
     a[0] = buf[base];
     cplx<T> w[R];
-    twiddle_powers<T, R>(w, j, twstep, tw);
+    if constexpr (READ)
+      twiddle_reads<T, R>(w, j, twstep, tw);
+    else
+      twiddle_powers<T, R>(w, j, twstep, tw);
 #pragma unroll
     for (int q = 1; q < R; ++q) a[q] = c_mulc(buf[base + q * step], w[q]);
   } else {
@@ -374,6 +446,41 @@ inline bool make_plan(int n, FftPlan& pl) {
     for (int i = 0; i < kMaxFactors; ++i) pl.radix[i] = i < k ? out[i] : 0;
     pl.nf = k;
   }
+  return true;
+}
+
+// Plan of the run-time kernels: the fewest stages of radix 2 to 10 (with `big` also
+// 12, 14, 15, 16), of those the one with the smallest largest radix, radices ascending
+// (the largest in the stride-1 stage without twiddles).
+inline bool make_wide_plan(int n, bool big, FftPlan& pl) {
+  pl.n = n;
+  pl.nf = 0;
+  for (int i = 0; i < kMaxFactors; ++i) pl.radix[i] = 0;
+  if (n < 1) return false;
+  const int radices[] = {2, 3, 4, 5, 6, 7, 8, 9, 10, 12, 14, 15, 16};
+  const int count = big ? 13 : 9;
+  int best[kMaxFactors], stack[kMaxFactors];
+  int best_nf = kMaxFactors + 1;
+  // depth-first over non-increasing radices
+  auto search = [&](auto&& self, int m, int depth, int limit) -> void {
+    if (m == 1) {
+      if (depth < best_nf || (depth == best_nf && depth > 0 && stack[0] < best[0])) {
+        best_nf = depth;
+        for (int i = 0; i < depth; ++i) best[i] = stack[i];
+      }
+      return;
+    }
+    if (depth >= kMaxFactors || depth >= best_nf) return;
+    for (int k = limit; k >= 0; --k)
+      if (m % radices[k] == 0) {
+        stack[depth] = radices[k];
+        self(self, m / radices[k], depth + 1, k);
+      }
+  };
+  search(search, n, 0, count - 1);
+  if (best_nf > kMaxFactors) return false;
+  pl.nf = best_nf;
+  for (int i = 0; i < best_nf; ++i) pl.radix[i] = best[best_nf - 1 - i];
   return true;
 }
 

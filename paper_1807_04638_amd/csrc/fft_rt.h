@@ -49,11 +49,11 @@ inline bool make_rt_plan(const FftPlan& pl, RtPlan& r) {
   return true;
 }
 
-// True if a plan holds a radix-16 stage: those take the kernels' BIG form (the
-// others keep the registers of a radix-9 butterfly).
-inline bool has_radix16(const FftPlan& pl) {
+// True if a plan holds a radix above 10: those take the kernels' BIG form (the others
+// keep the registers of a radix-10 butterfly).
+inline bool has_big_radix(const FftPlan& pl) {
   for (int i = 0; i < pl.nf; ++i)
-    if (pl.radix[i] == 16) return true;
+    if (pl.radix[i] > 10) return true;
   return false;
 }
 

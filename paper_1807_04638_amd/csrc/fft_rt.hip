@@ -25,12 +25,17 @@ namespace {
     case 3: CALL(3); break;     \
     case 4: CALL(4); break;     \
     case 5: CALL(5); break;     \
+    case 6: CALL(6); break;     \
     case 7: CALL(7); break;     \
     case 8: CALL(8); break;     \
     case 9: CALL(9); break;     \
+    case 10: CALL(10); break;   \
     default:                    \
       if constexpr (BIG) {      \
-        CALL(16);               \
+        if (r == 12) CALL(12);  \
+        if (r == 14) CALL(14);  \
+        if (r == 15) CALL(15);  \
+        if (r == 16) CALL(16);  \
       }                         \
       break;                    \
   }
@@ -61,9 +66,9 @@ __device__ __forceinline__ void rt_stage_r(cplx<T>* buf, const RtStage& s, int t
     const int j = TW ? u - mul24(blk, s.S) : 0;
     const int base = mul24(q, ss) + mul24(mul24(blk, s.L) + j, es);
     if (INV)
-      dit_butterfly<T, R, TW>(buf, base, s.S * es, j, s.tws, tw);
+      dit_butterfly<T, R, TW, true>(buf, base, s.S * es, j, s.tws, tw);
     else
-      dif_butterfly<T, R, TW>(buf, base, s.S * es, j, s.tws, tw);
+      dif_butterfly<T, R, TW, true>(buf, base, s.S * es, j, s.tws, tw);
   }
 }
 
@@ -163,7 +168,7 @@ __device__ __forceinline__ void rt_rows_first(cplx<T>* A, const cplx<T>* __restr
       A[base] = v[k][0];
       cplx<T> w[R];
       // the table in global memory: the LDS copy is complete only after the barrier
-      twiddle_powers<T, R>(w, j[k], 1, a.tw2);
+      twiddle_reads<T, R>(w, j[k], 1, a.tw2);
 #pragma unroll
       for (int q = 1; q < R; ++q) A[base + q * s.S] = s.S > 1 ? c_mul(v[k][q], w[q]) : v[k][q];
     }
@@ -181,7 +186,7 @@ __device__ __forceinline__ void rt_rows_last(const cplx<T>* A, cplx<T>* __restri
     const int r = index_quot(b, s.invS), j = b - mul24(r, s.S);
     const int base = mul24(r, a.LM) + j, o = mul24(r, rs) + j;
     cplx<T> v[R], w[R];
-    twiddle_powers<T, R>(w, j, 1, tw2);
+    twiddle_reads<T, R>(w, j, 1, tw2);
     v[0] = A[base];
 #pragma unroll
     for (int q = 1; q < R; ++q) v[q] = s.S > 1 ? c_mulc(A[base + q * s.S], w[q]) : A[base + q * s.S];
@@ -440,7 +445,7 @@ __device__ __forceinline__ void rt_pencil_first(cplx<T>* A, const cplx<T>* __res
       for (int h = 0; h < XS; ++h) v[h][q] = y[h];
     }
     cplx<T> w[R];
-    twiddle_powers<T, R>(w, j, 1, a.tw);
+    twiddle_reads<T, R>(w, j, 1, a.tw);
 #pragma unroll
     for (int h = 0; h < XS; ++h) {
       Dft<T, R, -1>::run(v[h]);
@@ -462,7 +467,7 @@ __device__ __forceinline__ void rt_pencil_last(const cplx<T>* A, cplx<T>* __rest
     const unsigned o = unsigned(j) * unsigned(a.es) + t;
     cplx<T> v[XS][R], w[R];
     const cplx<T> wx = XS > 1 ? a.twx[index_quot(q0 + t, a.inv_M)] : cplx<T>{T(1), T(0)};
-    twiddle_powers<T, R>(w, j, 1, tw);
+    twiddle_reads<T, R>(w, j, 1, tw);
 #pragma unroll
     for (int h = 0; h < XS; ++h) {
       const cplx<T>* x = A + mul24(j, ts) + h * tb + t;

@@ -57,13 +57,15 @@ int fold(int k, int n) { return k <= n - k ? k * k : (n - k) * (n - k); }
 // out = [add + add_scale *] K or L of `in` (ncomp components) with the three
 // passes, xs units per plane, tb groups per pencil workgroup.
 template <typename T>
-int apply(const int n[3], int ncomp, int xs, int tb, int threads, int xcd_run, double alpha, int s, int op,
+int apply(const int n[3], int ncomp, int xs, int tb, int threads, int xcd_run, double alpha, int s, int op, int wide,
           const T* in, const T* add, double add_scale, T* out) {
   const int n0 = n[0], n1 = n[1], H = n[2] / 2, M = H + 1, u1 = n1 / xs, P = n1 * M;
   FftPlan p0, p1, p2;
   RtPlaneArgs<T> a{};
   RtPencilArgs<T> k{};
-  if (n1 % xs || !make_plan(n0, p0) || !make_plan(u1, p1) || !make_plan(H, p2)) return 1;
+  // wide 0: the compile-time kernels' plans, 1: radices 2 to 10, 2: up to 16
+  auto plan = [&](int m, FftPlan& p) { return wide ? make_wide_plan(m, wide > 1, p) : make_plan(m, p); };
+  if (n1 % xs || !plan(n0, p0) || !plan(u1, p1) || !plan(H, p2)) return 1;
   if (!make_rt_plan(p0, k.r0) || !make_rt_plan(p1, a.r1) || !make_rt_plan(p2, a.r2)) return 2;
   const auto tw0 = roots<T>(n0, n0), tw1 = roots<T>(u1, u1), tw2 = roots<T>(H, H), twr = roots<T>(n[2], H / 2 + 1);
   std::vector<int> slot2(H + 1, H);
@@ -95,9 +97,9 @@ int apply(const int n[3], int ncomp, int xs, int tb, int threads, int xcd_run, d
   const size_t plane_lds = size_t(u1) * a.LM * c + (u1 + H + H / 2 + 1) * c + (H + 1) * sizeof(int);
   const size_t pencil_lds = (size_t(n0) * groups * xs + n0) * c + size_t(n0 + groups * xs) * sizeof(T);
   if (plane_lds > sizeof(smem) || pencil_lds > sizeof(smem)) return 3;
-  const auto fwd = rt_plane_fwd<T>(has_radix16(p1) || has_radix16(p2));
-  const auto inv = rt_plane_inv<T>(has_radix16(p1) || has_radix16(p2));
-  const auto pen = rt_pencil<T>(xs, has_radix16(p0));
+  const auto fwd = rt_plane_fwd<T>(has_big_radix(p1) || has_big_radix(p2));
+  const auto inv = rt_plane_inv<T>(has_big_radix(p1) || has_big_radix(p2));
+  const auto pen = rt_pencil<T>(xs, has_big_radix(p0));
   launch(n0 * xs, ncomp, threads, plane_lds, [&] { fwd(in, spec.data(), a); });
   launch((k.nin + groups - 1) / groups, ncomp, threads, pencil_lds, [&] { pen(spec.data(), k); });
   launch(n0 * xs, ncomp, threads, plane_lds, [&] { inv(spec.data(), out, a); });
@@ -109,7 +111,7 @@ int apply(const int n[3], int ncomp, int xs, int tb, int threads, int xcd_run, d
 #include <cstdio>
 #include <cstdlib>
 
-// argv: n0 n1 n2 ncomp xs tb threads xcd_run s op f64 add; doubles in (and the
+// argv: n0 n1 n2 ncomp xs tb threads xcd_run s op f64 add wide; doubles in (and the
 // addend) from stdin, doubles out on stdout.
 template <typename T>
 int run(char** v, const int n[3]) {
@@ -119,7 +121,7 @@ int run(char** v, const int n[3]) {
   if (std::fread(raw.data(), sizeof(double), raw.size(), stdin) != raw.size()) return 10;
   std::vector<T> in(raw.begin(), raw.begin() + N), add(raw.begin() + (raw.size() - N), raw.end()), out(N);
   const int rc = apply<T>(n, std::atoi(v[4]), std::atoi(v[5]), std::atoi(v[6]), std::atoi(v[7]), std::atoi(v[8]),
-                          0.0025, std::atoi(v[9]), std::atoi(v[10]), in.data(), with_add ? add.data() : nullptr, 0.3,
+                          0.0025, std::atoi(v[9]), std::atoi(v[10]), std::atoi(v[13]), in.data(), with_add ? add.data() : nullptr, 0.3,
                           out.data());
   if (rc) return rc;
   const std::vector<double> o(out.begin(), out.end());
@@ -128,7 +130,7 @@ int run(char** v, const int n[3]) {
 }
 
 int main(int argc, char** v) {
-  if (argc != 13) return 11;
+  if (argc != 14) return 11;
   const int n[3] = {std::atoi(v[1]), std::atoi(v[2]), std::atoi(v[3])};
   return std::atoi(v[11]) ? run<double>(v, n) : run<float>(v, n);
 }

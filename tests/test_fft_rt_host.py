@@ -12,18 +12,25 @@ import pytest
 HERE = os.path.dirname(os.path.abspath(__file__))
 ROOT = os.path.dirname(HERE)
 
-# n0, n1, n2, components, units per plane, groups per pencil workgroup, lanes, XCD run, s, op (0 K, 1 L), add
+# n0, n1, n2, components, units per plane, groups per pencil workgroup, lanes, XCD run, s, op (0 K, 1 L), add; plan
+# (0: the compile-time kernels', 1: radices 2 to 10, 2: up to 16)
 CASES = [
-    ((6, 10, 14), 1, 2, 5, 32, 1, 2, 0, 0),     # x2: one stage of radix 7; x0 two stages
-    ((4, 7, 4), 1, 1, 3, 32, 1, 1, 0, 1),       # whole odd planes, H = 2, one stage everywhere
-    ((5, 12, 6), 3, 4, 4, 32, 2, 2, 1, 1),      # quarters, single-stage x0, H = 3
-    ((15, 9, 10), 1, 3, 4, 32, 8, 3, 0, 0),     # thirds, ragged last tile
-    ((21, 20, 70), 1, 2, 16, 64, 8, 2, 0, 1),   # H = 35 (odd)
-    ((18, 16, 36), 1, 2, 8, 64, 1, 2, 1, 0),    # radix 9 and 2
-    ((16, 30, 30), 1, 2, 16, 64, 2, 2, 0, 0),   # radices 2, 3, 5; x0 = 16 (8 x 2)
-    ((4, 256, 8), 1, 2, 4, 64, 1, 2, 0, 0),     # a radix-16 stage along x1
-    ((128, 4, 4), 1, 1, 1, 32, 1, 2, 0, 1),     # a radix-16 stage along x0, one pencil per tile
-    ((24, 28, 50), 1, 4, 3, 64, 4, 2, 0, 0),    # quarters of 7 rows, H = 25
+    ((6, 10, 14), 1, 2, 5, 32, 1, 2, 0, 0, 0),     # x2: one stage of radix 7; x0 two stages
+    ((4, 7, 4), 1, 1, 3, 32, 1, 1, 0, 1, 0),       # whole odd planes, H = 2, one stage everywhere
+    ((5, 12, 6), 3, 4, 4, 32, 2, 2, 1, 1, 0),      # quarters, single-stage x0, H = 3
+    ((15, 9, 10), 1, 3, 4, 32, 8, 3, 0, 0, 0),     # thirds, ragged last tile
+    ((21, 20, 70), 1, 2, 16, 64, 8, 2, 0, 1, 0),   # H = 35 (odd)
+    ((18, 16, 36), 1, 2, 8, 64, 1, 2, 1, 0, 0),    # radix 9 and 2
+    ((16, 30, 30), 1, 2, 16, 64, 2, 2, 0, 0, 0),   # radices 2, 3, 5; x0 = 16 (8 x 2)
+    ((4, 256, 8), 1, 2, 4, 64, 1, 2, 0, 0, 0),     # a radix-16 stage along x1
+    ((128, 4, 4), 1, 1, 1, 32, 1, 2, 0, 1, 0),     # a radix-16 stage along x0, one pencil per tile
+    ((24, 28, 50), 1, 4, 3, 64, 4, 2, 0, 0, 0),    # quarters of 7 rows, H = 25
+    ((10, 12, 60), 1, 2, 5, 32, 2, 2, 0, 1, 1),    # radices 10 (one stage along x0), 6, 5 x 6
+    ((54, 18, 18), 1, 1, 4, 64, 1, 2, 1, 0, 1),    # 6 x 9, 3 x 6 whole planes, 9
+    ((48, 20, 32), 1, 2, 4, 64, 1, 2, 0, 0, 1),    # 6 x 8, 10, 4 x 4
+    ((15, 24, 28), 1, 2, 5, 32, 1, 2, 0, 1, 2),    # 15, 12, 14 in one stage each
+    ((96, 10, 8), 1, 1, 2, 64, 1, 2, 0, 0, 2),     # 8 x 12
+    ((7, 210, 24), 1, 2, 4, 64, 1, 2, 0, 0, 2),    # 7 x 15 along x1
 ]
 
 
@@ -41,15 +48,15 @@ def exe(tmp_path_factory):
 
 
 @pytest.mark.parametrize("f64", [1, 0])
-@pytest.mark.parametrize("case", CASES, ids=lambda c: "x".join(map(str, c[0])) + f"-{c[2]}")
+@pytest.mark.parametrize("case", CASES, ids=lambda c: "x".join(map(str, c[0])) + f"-{c[2]}-{c[9]}")
 def test_passes_match_numpy(exe, case, f64):
-    n, ncomp, xs, tb, lanes, run, s, op, add = case
+    n, ncomp, xs, tb, lanes, run, s, op, add, wide = case
     rng = np.random.default_rng(sum(n))
     f = rng.standard_normal((ncomp,) + n)
     q = rng.standard_normal((ncomp,) + n)
     if not f64:
         f, q = f.astype(np.float32).astype(np.float64), q.astype(np.float32).astype(np.float64)
-    args = [*n, ncomp, xs, tb, lanes, run, s, op, f64, add]
+    args = [*n, ncomp, xs, tb, lanes, run, s, op, f64, add, wide]
     r = subprocess.run([exe] + [str(int(a)) for a in args], input=f.tobytes() + (q.tobytes() if add else b""),
                        capture_output=True, timeout=120)
     assert r.returncode == 0, r.stderr.decode()[-2000:]

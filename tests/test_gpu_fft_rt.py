@@ -28,6 +28,10 @@ pytestmark = pytest.mark.gpu
     ((8, 320, 288), {}, 1),                                           # quarters in FP32, split passes in FP64
     ((6, 256, 256), {}, 1),                                           # halves in FP32, quarters in FP64
     ((5, 225, 240), {}, 1),                                           # thirds
+    ((50, 96, 100), {}, 1),                                           # radices 5 10, 6 8
+    ((54, 36, 60), {}, 1),                                            # 6 9, 3 6, 5 6
+    ((6, 210, 240), {}, 1),                                           # 7 15 and 10 12 (units over 80 KB)
+    ((7, 224, 252), {}, 1),                                           # 8 14 and 9 14
 ])
 @pytest.mark.parametrize("dtype", DTYPES)
 def test_run_time_kernels(n, opts, cut, dtype):
