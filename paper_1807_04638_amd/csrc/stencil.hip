@@ -712,20 +712,12 @@ __global__ void __launch_bounds__(256)
   if (!HALO || nb.out) vstore3<T, VW>(dmu_out, mo, nb.o, g.N);
 }
 
-// ZS bit 2: the start value w0 is zero and not read (the sweep's first corrector).
-template <typename T, int VW, bool PAIR, bool HALO, int ZS = 0>
-__global__ void __launch_bounds__(256)
-    k_adjoint_stage_v(Geo<T> g, int RW, const T* __restrict__ U, const T* __restrict__ w, const T* __restrict__ mu,
-                      const T* __restrict__ v, const T* U0, const T* w0, T* __restrict__ Z, T* __restrict__ Q,
-                      T* U_out, T dt, T a0, T a1, const T* __restrict__ qadd, T qs) {
-  VNbr<VW> nb;
-  if (!vvoxel<T, VW, HALO>(g, RW, nb)) return;
-  T u[3][VW], vc[3][VW], wc[3][VW], m[3][VW];
-  vload3<T, VW>(u, U, nb.o, g.N);
-  vload3<T, VW>(vc, v, nb.o, g.N);
-  vload3<T, VW>(wc, w, nb.o, g.N);
-  vload3<T, VW>(m, mu, nb.o, g.N);
-  T z[3][VW] = {}, aU[3][VW] = {}, aw[3][VW] = {};
+// z += ad*_w mu, aw += ad_v w, aU += ad*_v U at each of the lane's voxels.
+template <typename T, int VW, bool PAIR>
+__device__ __forceinline__ void vadjoint_terms(const Geo<T>& g, const VNbr<VW>& nb, const T* __restrict__ w,
+                                               const T wc[3][VW], const T* __restrict__ mu, const T m[3][VW],
+                                               const T* __restrict__ v, const T vc[3][VW], const T* __restrict__ U,
+                                               const T u[3][VW], T z[3][VW], T aw[3][VW], T aU[3][VW]) {
 #pragma unroll
   for (int e = 0; e < 3; ++e) {
     const T h = vinv2h<T, VW, PAIR>(g, nb, e);
@@ -744,6 +736,23 @@ __global__ void __launch_bounds__(256)
       vadstar_dir<T, VW>(aU, Vp, Up, u, e, h);  // ad*_v U
     }
   }
+}
+
+// ZS bit 2: the start value w0 is zero and not read (the sweep's first corrector).
+template <typename T, int VW, bool PAIR, bool HALO, int ZS = 0>
+__global__ void __launch_bounds__(256)
+    k_adjoint_stage_v(Geo<T> g, int RW, const T* __restrict__ U, const T* __restrict__ w, const T* __restrict__ mu,
+                      const T* __restrict__ v, const T* U0, const T* w0, T* __restrict__ Z, T* __restrict__ Q,
+                      T* U_out, T dt, T a0, T a1, const T* __restrict__ qadd, T qs) {
+  VNbr<VW> nb;
+  if (!vvoxel<T, VW, HALO>(g, RW, nb)) return;
+  T u[3][VW], vc[3][VW], wc[3][VW], m[3][VW];
+  vload3<T, VW>(u, U, nb.o, g.N);
+  vload3<T, VW>(vc, v, nb.o, g.N);
+  vload3<T, VW>(wc, w, nb.o, g.N);
+  vload3<T, VW>(m, mu, nb.o, g.N);
+  T z[3][VW] = {}, aU[3][VW] = {}, aw[3][VW] = {};
+  vadjoint_terms<T, VW, PAIR>(g, nb, w, wc, mu, m, v, vc, U, u, z, aw, aU);
   T q[3][VW], uo[3][VW];
 #pragma unroll
   for (int c = 0; c < 3; ++c)
@@ -761,6 +770,15 @@ __global__ void __launch_bounds__(256)
   if (!HALO || nb.out) vstore3<T, VW>(U_out, uo, nb.o, g.N);
 }
 
+// Bound by the L1 data unit: eight stencil fields, 24 components of four or five VW-wide
+// loads each. The first-order and the incremental adjoint terms are the same expressions
+// of four fields, so the kernel runs the adjoint stage's body twice, in a loop that is
+// not unrolled: unrolled, the compiler holds both parts' loads at once (FP32, 4 voxels a
+// lane: 256 + 76 registers, one wave per SIMD; in the loop 148, three), which once kept
+// the kernel to two voxels a lane. FP32 96^3 at 3 voxels a lane 35.8 us (two voxels,
+// unrolled 50.6), 128^3 at 4 78 (99), 180 x 210 x 180 312 (397); FP64 128^3 173 (189).
+// One voxel a lane fits 128 registers with both parts in flight and gains from it (32^3
+// 5.5 us, in the loop 6.7).
 template <typename T, int VW, bool PAIR, bool HALO>
 __global__ void __launch_bounds__(256)
     k_newton_stage_v(Geo<T> g, int RW, const T* __restrict__ dU, const T* __restrict__ dw, const T* __restrict__ mu,
@@ -769,46 +787,18 @@ __global__ void __launch_bounds__(256)
                      T* __restrict__ Z, T* __restrict__ Q, T* dU_out, T dt, T a0, T a1) {
   VNbr<VW> nb;
   if (!vvoxel<T, VW, HALO>(g, RW, nb)) return;
-  T du[3][VW], dwc[3][VW], m[3][VW], w1c[3][VW], dm[3][VW], vc[3][VW], wk[3][VW], u1[3][VW];
-  vload3<T, VW>(du, dU, nb.o, g.N);
-  vload3<T, VW>(dwc, dw, nb.o, g.N);
-  vload3<T, VW>(m, mu, nb.o, g.N);
-  vload3<T, VW>(w1c, w1, nb.o, g.N);
-  vload3<T, VW>(dm, dmu, nb.o, g.N);
-  vload3<T, VW>(vc, v, nb.o, g.N);
-  vload3<T, VW>(wk, Wv, nb.o, g.N);
-  vload3<T, VW>(u1, U1, nb.o, g.N);
   T z[3][VW] = {}, aU[3][VW] = {}, aw[3][VW] = {};
-#pragma unroll
-  for (int e = 0; e < 3; ++e) {
-    const T h = vinv2h<T, VW, PAIR>(g, nb, e);
-    VPair<T, VW> Dwp, Vp, W1p, Wkp;
-    vpair<T, VW, PAIR>(Dwp, dw, dwc, nb, e, g.N);
-    {
-      VPair<T, VW> Mp;
-      vpair<T, VW, PAIR>(Mp, mu, m, nb, e, g.N);
-      vadstar_dir<T, VW>(z, Dwp, Mp, m, e, h);  // ad*_dw mu
-    }
-    vpair<T, VW, PAIR>(Vp, v, vc, nb, e, g.N);
-    vad_dir<T, VW>(aw, Vp, Dwp, vc, dwc, e, h);  // ad_v dw
-    {
-      VPair<T, VW> Dp;
-      vpair<T, VW, PAIR>(Dp, dU, du, nb, e, g.N);
-      vadstar_dir<T, VW>(aU, Vp, Dp, du, e, h);  // ad*_v dU
-    }
-    vpair<T, VW, PAIR>(W1p, w1, w1c, nb, e, g.N);
-    {
-      VPair<T, VW> Dmp;
-      vpair<T, VW, PAIR>(Dmp, dmu, dm, nb, e, g.N);
-      vadstar_dir<T, VW>(z, W1p, Dmp, dm, e, h);  // ad*_w1 dmu
-    }
-    vpair<T, VW, PAIR>(Wkp, Wv, wk, nb, e, g.N);
-    vad_dir<T, VW>(aw, Wkp, W1p, wk, w1c, e, h);  // ad_W w1
-    {
-      VPair<T, VW> Ap;
-      vpair<T, VW, PAIR>(Ap, U1, u1, nb, e, g.N);
-      vadstar_dir<T, VW>(aU, Wkp, Ap, u1, e, h);  // ad*_W U1
-    }
+  T du[3][VW], dwc[3][VW];
+  const T *fw = w1, *fm = dmu, *fv = Wv, *fu = U1;  // ad*_w1 dmu, ad_W w1, ad*_W U1
+#pragma unroll(VW == 1 ? 2 : 1)
+  for (int part = 0; part < 2; ++part) {
+    T m[3][VW], vc[3][VW];
+    vload3<T, VW>(du, fu, nb.o, g.N);
+    vload3<T, VW>(dwc, fw, nb.o, g.N);
+    vload3<T, VW>(m, fm, nb.o, g.N);
+    vload3<T, VW>(vc, fv, nb.o, g.N);
+    vadjoint_terms<T, VW, PAIR>(g, nb, fw, dwc, fm, m, fv, vc, fu, du, z, aw, aU);
+    fw = dw, fm = mu, fv = v, fu = dU;  // ad*_dw mu, ad_v dw, ad*_v dU
   }
   T q[3][VW], uo[3][VW];
 #pragma unroll
@@ -836,16 +826,13 @@ struct RowShape {
   dim3 grid, block;
 };
 
-// max_vw: kernels with more stencil fields take at most so many voxels per lane (to
-// keep their registers in bounds).
 template <typename T>
-RowShape<T> row_shape(const Grid& g, int max_vw = 4) {
+RowShape<T> row_shape(const Grid& g) {
   RowShape<T> s;
-  if (g.segvec) {
-    s.VW = g.segvec <= max_vw ? g.segvec : max_vw;
-  } else if (row_vector_valid(g.n2, g.rowvec)) {
-    s.VW = g.rowvec <= max_vw ? g.rowvec : row_vector_valid(g.n2, max_vw) ? max_vw : 0;
-  }
+  if (g.segvec)
+    s.VW = g.segvec;
+  else if (row_vector_valid(g.n2, g.rowvec))
+    s.VW = g.rowvec;
   if (!s.VW) return s;
   s.RW = g.n2 / s.VW;
   s.geo = make_geo<T>(g);
@@ -868,8 +855,8 @@ RowShape<T> row_shape(const Grid& g, int max_vw = 4) {
 template <int V>
 using Int = std::integral_constant<int, V>;
 
-// f(VW, PAIR, HALO) as compile-time constants; widths above MAX are not instantiated.
-template <int MAX, typename T, class F>
+// f(VW, PAIR, HALO) as compile-time constants.
+template <typename T, class F>
 void with_row_shape(const RowShape<T>& s, F f) {
   auto pair = [&](auto vw, auto halo) {
     if (s.pair)
@@ -880,10 +867,8 @@ void with_row_shape(const RowShape<T>& s, F f) {
   if (s.halo) return pair(Int<2>(), std::true_type());  // cut rows: width 2
   if (s.VW == 1) return pair(Int<1>(), std::false_type());
   if (s.VW == 2) return pair(Int<2>(), std::false_type());
-  if constexpr (MAX >= 4) {
-    if (s.VW == 3) return pair(Int<3>(), std::false_type());
-    return pair(Int<4>(), std::false_type());
-  }
+  if (s.VW == 3) return pair(Int<3>(), std::false_type());
+  return pair(Int<4>(), std::false_type());
 }
 
 dim3 ft_grid(const Grid& g) { return dim3(make_field_tiling(g).blocks); }
@@ -905,7 +890,7 @@ void launch_epdiff_stage(const Grid& g, const T* v, const T* mu, const T* mu0, T
   KernelTimer t(prof, a0 != 0.0 ? "epdiff_stage_corr" : "epdiff_stage_pred");
   const RowShape<T> s = row_shape<T>(g);
   if (s.VW) {
-    with_row_shape<4>(s, [&](auto vw, auto pair, auto halo) {
+    with_row_shape(s, [&](auto vw, auto pair, auto halo) {
       LDDMM_LAUNCH(t.start, t.stop, (k_epdiff_stage_v<T, vw, pair, halo>), s.grid, s.block, 0, st, s.geo, s.RW, v, mu, mu0 ? mu0 : mu, mu_out, T(dt), T(a0), T(a1));
     });
     return;
@@ -922,7 +907,7 @@ void launch_tangent_stage(const Grid& g, const T* X, const T* dmu, const T* W, c
   KernelTimer t(prof, a0 != 0.0 ? (zs ? "tangent_stage_corr_first" : "tangent_stage_corr")
                                 : (zs ? "tangent_stage_pred_first" : "tangent_stage_pred"));
   if (s.VW) {
-    with_row_shape<4>(s, [&](auto vw, auto pair, auto halo) {
+    with_row_shape(s, [&](auto vw, auto pair, auto halo) {
       auto launch = [&](auto z) {
         LDDMM_LAUNCH(t.start, t.stop, (k_tangent_stage_v<T, vw, pair, halo, z>), s.grid, s.block, 0, st, s.geo, s.RW, X, dmu, W, v, mu, X0 ? X0 : X, dmu0 ? dmu0 : dmu, X_out, dmu_out, T(dt), T(a0), T(a1), Gfin, T(cfin));
       };
@@ -946,7 +931,7 @@ void launch_adjoint_stage(const Grid& g, const T* U, const T* w, const T* mu, co
   const bool zs = zero != 0 && s.VW;  // the zero-start variant runs
   KernelTimer t(prof, a0 != 0.0 ? (zs ? "adjoint_stage_corr_first" : "adjoint_stage_corr") : "adjoint_stage_pred");
   if (s.VW) {
-    with_row_shape<4>(s, [&](auto vw, auto pair, auto halo) {
+    with_row_shape(s, [&](auto vw, auto pair, auto halo) {
       auto launch = [&](auto z) {
         LDDMM_LAUNCH(t.start, t.stop, (k_adjoint_stage_v<T, vw, pair, halo, z>), s.grid, s.block, 0, st, s.geo, s.RW, U, w, mu, v, U0 ? U0 : U, w0 ? w0 : w, Z, Q, U_out, T(dt), T(a0), T(a1), qadd, T(qs));
       };
@@ -984,9 +969,9 @@ void launch_newton_stage(const Grid& g, const T* dU, const T* dw, const T* mu, c
                          const T* Wv, const T* U1, const T* dU0, const T* dw0, T* Z, T* Q, T* dU_out, double dt,
                          double a0, double a1, hipStream_t st, Profiler* prof) {
   KernelTimer t(prof, a0 != 0.0 ? "newton_stage_corr" : "newton_stage_pred");
-  const RowShape<T> s = row_shape<T>(g, 2);  // eight stencil fields
+  const RowShape<T> s = row_shape<T>(g);
   if (s.VW) {
-    with_row_shape<2>(s, [&](auto vw, auto pair, auto halo) {
+    with_row_shape(s, [&](auto vw, auto pair, auto halo) {
       LDDMM_LAUNCH(t.start, t.stop, (k_newton_stage_v<T, vw, pair, halo>), s.grid, s.block, 0, st, s.geo, s.RW, dU, dw, mu, w1, dmu, v, Wv, U1, dU0 ? dU0 : dU, dw0 ? dw0 : dw, Z, Q, dU_out, T(dt), T(a0), T(a1));
     });
     return;
