@@ -699,7 +699,7 @@ class Engine {
     const long long V = 3 * N;
     for (auto* vec : {&nU1, &nW1, &nU2, &nW2, &tdmu, &tdmuK, &tdmus, &tdmusK}) {
       vec->assign(P.nt, nullptr);
-      for (int n = 0; n < P.nt; ++n)
+      for (int n = vec == &tdmuK ? 1 : 0; n < P.nt; ++n)  // K dmu_0 is dv itself
         if (alloc(&(*vec)[n], V)) {
           for (auto* w : {&nU1, &nW1, &nU2, &nW2, &tdmu, &tdmuK, &tdmus, &tdmusK}) w->clear();
           return fail(LDDMM_ENOMEM, "cannot allocate the Newton stage histories");
@@ -708,38 +708,39 @@ class Engine {
     return 0;
   }
 
-  // The gradient's adjoint sweep, keeping its state at each stage input.
+  // The gradient's adjoint sweep, each stage writing its result where the Newton sweep
+  // reads it (copying it there took 64 fields and 7 % of a product with its linearization
+  // at 96^3 FP32). The last corrector's result is not an input of any stage.
   void backward_record() {
-    const long long V = 3 * N;
-    launch_scalar_times_vec<T>(g, res, G, -2.0 / P.sigma2, U, st, &prof);
-    launch_fill<T>(V, T(0), Wh, st, &prof);
+    launch_scalar_times_vec<T>(g, res, G, -2.0 / P.sigma2, nU1[P.nt - 1], st, &prof);
+    launch_fill<T>(3 * N, T(0), nW1[P.nt - 1], st, &prof);
     for (int n = P.nt - 1; n >= 0; --n) {
       const Step c = traj_view(n);
-      copy(nU1[n], U, V);
-      copy(nW1[n], Wh, V);
-      adjoint_pred(c);
-      copy(nU2[n], Us, V);
-      copy(nW2[n], Whs, V);
-      adjoint_corr(c);
+      launch_adjoint_stage<T>(g, nU1[n], nW1[n], c.mus, c.vs, nullptr, nullptr, Z, Qw, nU2[n], dt, 0.0, 1.0, st,
+                              &prof);
+      applyK_add(Z, Qw, dt, nW2[n]);
+      if (n == 0) break;
+      launch_adjoint_stage<T>(g, nU2[n], nW2[n], c.mu, c.v, nU1[n], nW1[n], Z, Qw, nU1[n - 1], dt, 0.5, 0.5, st,
+                              &prof);
+      applyK_add(Z, Qw, 0.5 * dt, nW1[n - 1]);
     }
   }
 
-  // The tangent sweep, keeping the trajectory variation at each stage point.
+  // The tangent sweep, keeping the trajectory variation at each stage point (but K dmu_0
+  // = K L dv, which is dv itself).
   void tangent_record(const T* dv) {
-    const long long V = 3 * N;
-    applyL(dv, Mu);
-    launch_fill<T>(V, T(0), X, st, &prof);
+    applyL(dv, tdmu[0]);
+    const bool zs = stencil_zero_start(g);
+    if (!zs) launch_fill<T>(3 * N, T(0), X, st, &prof);
     for (int n = 0; n < P.nt; ++n) {
       const Step c = traj_view(n);
-      copy(tdmu[n], Mu, V);
-      if (n > 0)
-        applyK(Mu, tdmuK[n]);
-      else
-        copy(tdmuK[0], dv, V);  // K L dv = dv
-      launch_tangent_stage<T>(g, X, Mu, tdmuK[n], c.v, c.mu, nullptr, nullptr, Xs, Mus, dt, 0.0, 1.0, st, &prof);
-      copy(tdmus[n], Mus, V);
-      applyK(Mus, tdmusK[n]);
-      launch_tangent_stage<T>(g, Xs, Mus, tdmusK[n], c.vs, c.mus, X, Mu, X, Mu, dt, 0.5, 0.5, st, &prof);
+      const bool z0 = n == 0 && zs;
+      if (n > 0) applyK(tdmu[n], tdmuK[n]);
+      launch_tangent_stage<T>(g, X, tdmu[n], n > 0 ? tdmuK[n] : dv, c.v, c.mu, nullptr, nullptr, Xs, tdmus[n], dt,
+                              0.0, 1.0, st, &prof, nullptr, 0.0, z0 ? 1 : 0);
+      applyK(tdmus[n], tdmusK[n]);
+      launch_tangent_stage<T>(g, Xs, tdmus[n], tdmusK[n], c.vs, c.mus, X, tdmu[n], X,
+                              n + 1 < P.nt ? tdmu[n + 1] : Mu, dt, 0.5, 0.5, st, &prof, nullptr, 0.0, z0 ? 2 : 0);
     }
   }
 
@@ -757,8 +758,8 @@ class Engine {
       launch_newton_stage<T>(g, U, Wh, c.mus, nW1[n], tdmus[n], c.vs, tdmusK[n], nU1[n], nullptr, nullptr, Z, Qw,
                              Us, dt, 0.0, 1.0, st, &prof);
       applyK_add(Z, Qw, dt, Whs);
-      launch_newton_stage<T>(g, Us, Whs, c.mu, nW2[n], tdmu[n], c.v, tdmuK[n], nU2[n], U, Wh, Z, Qw, U, dt, 0.5, 0.5,
-                             st, &prof);
+      launch_newton_stage<T>(g, Us, Whs, c.mu, nW2[n], tdmu[n], c.v, n > 0 ? tdmuK[n] : dv, nU2[n], U, Wh, Z, Qw, U,
+                             dt, 0.5, 0.5, st, &prof);
       applyK_add(Z, Qw, 0.5 * dt, Wh);
     }
     launch_axpbyz<T>(3 * N, 2.0, dv, 1.0, Wh, hv, st, &prof);
