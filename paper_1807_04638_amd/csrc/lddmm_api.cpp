@@ -1491,6 +1491,8 @@ class Engine {
   std::vector<T*> pm, pD;              // m_n and div v_n, n = 0..nt
   T *plam[2] = {nullptr, nullptr}, *pdm[2] = {nullptr, nullptr}, *psrc[2] = {nullptr, nullptr};
   double pE = 0, pEreg = 0, pEdata = 0;
+  int pbatch = 1;         // time points per spectral pass
+  cplx<T>* pspec = nullptr;  // their spectra (pbatch > 1)
 
   int pde_slices(bool stationary) const { return stationary ? 1 : P.nt + 1; }
   // quadrature weight of time point n (trapezoid, dt)
@@ -1508,8 +1510,33 @@ class Engine {
         if (alloc(&q, N)) return fail(LDDMM_ENOMEM, "out of device memory (PDE-LDDMM workspace)");
     for (T** q : {&plam[0], &plam[1], &pdm[0], &pdm[1], &psrc[0], &psrc[1]})
       if (alloc(q, N)) return fail(LDDMM_ENOMEM, "out of device memory (PDE-LDDMM workspace)");
+    // Spectral passes over a stack take several time points per launch: at small grids
+    // one field's pass is launch latency, and larger launches end in fewer half-empty
+    // waves.  An energy, gradient and Hessian product over 11 time points, FP32: 64^3 33
+    // passes of 16 us, now 2 of 54; 128^3 33 of 38, now 8 of 86.  Their spectra stay within
+    // a share of the 256 MB cache; without memory for them one field at a time.
+    const size_t one = spectrum_bytes(sp, 3);
+    pbatch = int(std::min<size_t>({size_t(96) << 20, one * (P.nt + 1), one * 256}) / one);
+    if (pbatch > 1) {
+      T* q = nullptr;
+      if (alloc(&q, (long long)(pbatch * one / sizeof(T)))) {
+        (void)hipGetLastError();
+        pbatch = 1;
+      }
+      pspec = reinterpret_cast<cplx<T>*>(q);
+    }
+    if (pbatch < 1) pbatch = 1;
     pde_ready = true;
     return 0;
+  }
+  // out = scale * K or L applied to each of the ns fields of a stack
+  void pde_spectral(const T* in, T* out, int ns, int op, double scale = 1.0) {
+    SpectralPlan<T> b = sp;
+    if (pbatch > 1) b.spec = pspec;
+    for (int n = 0; n < ns; n += pbatch) {
+      const int k = std::min(pbatch, ns - n);
+      spectral_apply<T>(b, in + n * 3 * N, out + n * 3 * N, 3 * k, P.alpha, P.s, op, st, &prof, nullptr, 0.0, scale);
+    }
   }
   // time point n of a stack (every point is the single field when stationary)
   const T* slice(const T* stack, int n, bool stationary) const {
@@ -1517,18 +1544,29 @@ class Engine {
   }
   T* slice(T* stack, int n, bool stationary) const { return stationary ? stack : stack + (long long)n * 3 * N; }
 
-  // FP64 space-time L2 product sum_n w_n <a_n, b_n> of two stacks (synchronising)
-  double pde_dot(const T* a, const T* b, bool stationary) {
+  // FP64 space-time L2 product sum_n w_n <a_n, b_n> of two stacks: the sums of the first,
+  // the inner and the last time points into dres[12 .. 14], enqueued only
+  void pde_dot_dev(const T* a, const T* b, bool stationary) {
     const long long V = 3 * N;
-    if (stationary) return dot(a, b);
-    dot_dev(a, b, 3 * (P.nt + 1), 12);                                  // all time points
-    launch_dot(a, b, V, partials, dres + 13, st, &prof);                  // t = 0
-    launch_dot(a + P.nt * V, b + P.nt * V, V, partials, dres + 14, st, &prof);  // t = 1
+    launch_dot(a, b, V, partials, dres + 12, st, &prof);
+    if (stationary) return;
+    if (P.nt > 1) launch_dot(a + V, b + V, (P.nt - 1) * V, partials, dres + 13, st, &prof);
+    launch_dot(a + P.nt * V, b + P.nt * V, V, partials, dres + 14, st, &prof);
+  }
+  // the product from the sums on the host
+  double pde_dot_host(bool stationary) const {
+    if (stationary) return cell * hres[12];
+    const double inner = P.nt > 1 ? hres[13] : 0.0;
+    return cell * dt * (0.5 * hres[12] + inner + 0.5 * hres[14]);
+  }
+  double pde_dot(const T* a, const T* b, bool stationary) {
+    pde_dot_dev(a, b, stationary);
     post_fetch();
     wait();
-    return cell * dt * (hres[12] - 0.5 * hres[13] - 0.5 * hres[14]);
+    return pde_dot_host(stationary);
   }
-  // state sweep, divergences and both energy terms at the stack v (copied)
+  // state sweep, divergences and both energy terms at the stack v (copied); leaves L v
+  // in pq for the gradient
   void pde_linearize(const T* v, bool stationary) {
     const long long V = 3 * N;
     const int ns = pde_slices(stationary);
@@ -1537,39 +1575,45 @@ class Engine {
     for (int n = 0; n < P.nt; ++n)
       launch_pde_state<T>(g, pm[n], slice(pv, n, stationary), slice(pv, n + 1, stationary), pm[n + 1], dt, st, &prof);
     for (int n = 0; n < ns; ++n) launch_div<T>(g, slice(pv, n, stationary), pD[n], st, &prof);
-    // regulariser: <L v, v> (stationary) or sum_n w_n <L v_n, v_n>
-    double ereg = 0;
-    for (int n = 0; n < ns; ++n) {
-      applyL(slice(pv, n, stationary), pacc);
-      const double d = dot(pacc, slice(pv, n, stationary));
-      ereg += stationary ? d : pde_w(n) * d;
-    }
+    // regulariser <L v, v> (stationary) or sum_n w_n <L v_n, v_n>, and the data term; one
+    // synchronisation for both
+    pde_spectral(pv, pq, ns, LDDMM_OP_L);
+    pde_dot_dev(pq, pv, stationary);
     launch_axpbyz<T>(N, 1.0, pm[P.nt], -1.0, I1, tmpS, st, &prof);
-    pEreg = ereg;
-    pEdata = dot(tmpS, tmpS, 1) / P.sigma2;
+    dot_dev(tmpS, tmpS, 1, 15);
+    post_fetch();
+    wait();
+    pEreg = pde_dot_host(stationary);
+    pEdata = cell * hres[15] / P.sigma2;
     pE = pEreg + pEdata;
     pde_lin = true;
     pde_stat = stationary;
   }
   // Backward sweep of a final lambda in plam[nt & 1]: out = 2 L base + sum over
   // time of lambda_n grad m_n (per time point, or its time integral when stationary).
-  void pde_backward(const T* base, T* out, bool stationary) {
+  // Lbase: L base when the caller has it (the gradient, whose energy applied L to v).
+  void pde_backward(const T* base, const T* Lbase, T* out, bool stationary) {
     const long long V = 3 * N;
-    if (stationary) launch_fill<T>(V, T(0), pacc, st, &prof);
+    if (stationary)
+      launch_fill<T>(V, T(0), pacc, st, &prof);
+    else if (!Lbase)
+      pde_spectral(base, out, P.nt + 1, LDDMM_OP_L, 2.0);  // 2 L base_n
     for (int n = P.nt; n >= 0; --n) {
       const T* lam = plam[n & 1];
       if (n < P.nt)
         launch_pde_adjoint<T>(g, plam[(n + 1) & 1], pD[stationary ? 0 : n], pD[stationary ? 0 : n + 1],
                               slice(pv, n, stationary), slice(pv, n + 1, stationary), plam[n & 1], dt, st, &prof);
-      if (stationary) {
-        launch_pde_lambda_grad<T>(g, pm[n], lam, pde_w(n), pacc, st, &prof);
-      } else {
-        T* o = slice(out, n, false);
-        spectral(slice(base, n, false), o, 3, LDDMM_OP_L, nullptr, 0.0, 2.0);  // 2 L base_n
-        launch_pde_lambda_grad<T>(g, pm[n], lam, 1.0, o, st, &prof);
-      }
+      T* o = stationary ? pacc : slice(out, n, false);
+      if (!stationary && Lbase)
+        launch_pde_lambda_grad<T>(g, pm[n], lam, 1.0, 2.0, slice(Lbase, n, false), o, st, &prof);
+      else
+        launch_pde_lambda_grad<T>(g, pm[n], lam, stationary ? pde_w(n) : 1.0, 1.0, o, o, st, &prof);
     }
-    if (stationary) spectral(base, out, 3, LDDMM_OP_L, pacc, 2.0);  // pacc + 2 L base
+    if (!stationary) return;
+    if (Lbase)
+      launch_axpbyz<T>(V, 2.0, Lbase, 1.0, pacc, out, st, &prof);
+    else
+      spectral(base, out, 3, LDDMM_OP_L, pacc, 2.0);  // pacc + 2 L base
   }
   int pde_check(bool stationary) {
     if (!have_images) return fail(LDDMM_ESTATE, "images not set");
@@ -1584,9 +1628,10 @@ class Engine {
     if (energy) *energy = pE;
     return hip_status("pde_energy");
   }
+  // directly after pde_linearize (pq holds L v)
   void pde_gradient_core(T* gout) {
     launch_axpbyz<T>(N, -2.0 / P.sigma2, pm[P.nt], 2.0 / P.sigma2, I1, plam[P.nt & 1], st, &prof);
-    pde_backward(pv, gout, pde_stat);
+    pde_backward(pv, pq, gout, pde_stat);
   }
   int pde_gradient(bool stationary, const T* v, T* gout, double* energy) {
     if (int rc = pde_energy(stationary, v, nullptr, energy)) return rc;
@@ -1604,7 +1649,7 @@ class Engine {
                          slice(pv, n + 1, stationary), pdm[(n + 1) & 1], dt, st, &prof);
     }
     launch_axpbyz<T>(N, -2.0 / P.sigma2, pdm[P.nt & 1], 0.0, pdm[P.nt & 1], plam[P.nt & 1], st, &prof);
-    pde_backward(dv, hv, stationary);
+    pde_backward(dv, nullptr, hv, stationary);
   }
   int pde_hessvec(bool stationary, const T* v, const T* dv, T* hv) {
     if (int rc = pde_check(stationary)) return rc;
@@ -1618,7 +1663,7 @@ class Engine {
   }
   // K per time point
   void pde_precondition(const T* r, T* z, bool stationary) {
-    for (int n = 0; n < pde_slices(stationary); ++n) applyK(slice(r, n, stationary), slice(z, n, stationary));
+    pde_spectral(r, z, pde_slices(stationary), LDDMM_OP_K);
   }
   // PCG in the space-time L2 product for H x = -g, preconditioner K
   int pde_pcg(const T* gin, T* x, double eta, int maxit) {

@@ -244,10 +244,10 @@ void launch_pde_adjoint(const Grid& g, const T* lam_new, const T* D_old, const T
 // D = div_h v
 template <typename T>
 void launch_div(const Grid& g, const T* v, T* D, hipStream_t st, Profiler* prof);
-// out += w lam grad_h m
+// out = bs base + w lam grad_h m (base == out allowed)
 template <typename T>
-void launch_pde_lambda_grad(const Grid& g, const T* m, const T* lam, double w, T* out, hipStream_t st,
-                            Profiler* prof);
+void launch_pde_lambda_grad(const Grid& g, const T* m, const T* lam, double w, double bs, const T* base, T* out,
+                            hipStream_t st, Profiler* prof);
 // s = -grad_h m . dv
 template <typename T>
 void launch_pde_source(const Grid& g, const T* m, const T* dv, T* s, hipStream_t st, Profiler* prof);

@@ -329,11 +329,12 @@ __global__ void __launch_bounds__(256) k_div(SlGeo<T> g, const T* __restrict__ v
 }
 
 // With ssrc: s = -grad_h m . dv (the incremental state's source) into ssrc.
-// Else out += w lam grad_h m (a time point's term of the gradient or Hessian).
+// Else out = bs base + w lam grad_h m (a time point's term of the gradient or Hessian;
+// base may be out).
 template <typename T>
 __global__ void __launch_bounds__(256)
     k_pde_grad_m(SlGeo<T> g, const T* __restrict__ m, const T* __restrict__ lam, const T* __restrict__ dv, T w,
-                 T* __restrict__ out, T* __restrict__ ssrc) {
+                 T bs, const T* base, T* out, T* __restrict__ ssrc) {
   int i0, i1, i2;
   if (!tile_voxel(g.ft, g.n1, g.n2, i0, i1, i2)) return;
   const int s0 = g.n1 * g.n2;
@@ -348,7 +349,7 @@ __global__ void __launch_bounds__(256)
   }
   const T a = w * lam[o];
 #pragma unroll
-  for (int c = 0; c < 3; ++c) out[c * g.N + o] += a * gm[c];
+  for (int c = 0; c < 3; ++c) out[c * g.N + o] = bs * base[c * g.N + o] + a * gm[c];
 }
 
 }  // namespace
@@ -408,18 +409,18 @@ void launch_div(const Grid& g, const T* v, T* D, hipStream_t st, Profiler* prof)
 }
 
 template <typename T>
-void launch_pde_lambda_grad(const Grid& g, const T* m, const T* lam, double w, T* out, hipStream_t st,
-                            Profiler* prof) {
+void launch_pde_lambda_grad(const Grid& g, const T* m, const T* lam, double w, double bs, const T* base, T* out,
+                            hipStream_t st, Profiler* prof) {
   KernelTimer t(prof, "pde_lambda_grad_m");
   const FieldTiling ft = make_field_tiling(g);
-  LDDMM_LAUNCH(t.start, t.stop, k_pde_grad_m<T>, ft.blocks, dim3(ft.BX, ft.BY), 0, st, make_sl_geo<T>(g), m, lam, static_cast<const T*>(nullptr), T(w), out, static_cast<T*>(nullptr));
+  LDDMM_LAUNCH(t.start, t.stop, k_pde_grad_m<T>, ft.blocks, dim3(ft.BX, ft.BY), 0, st, make_sl_geo<T>(g), m, lam, static_cast<const T*>(nullptr), T(w), T(bs), base, out, static_cast<T*>(nullptr));
 }
 
 template <typename T>
 void launch_pde_source(const Grid& g, const T* m, const T* dv, T* s, hipStream_t st, Profiler* prof) {
   KernelTimer t(prof, "pde_source");
   const FieldTiling ft = make_field_tiling(g);
-  LDDMM_LAUNCH(t.start, t.stop, k_pde_grad_m<T>, ft.blocks, dim3(ft.BX, ft.BY), 0, st, make_sl_geo<T>(g), m, static_cast<const T*>(nullptr), dv, T(0), static_cast<T*>(nullptr), s);
+  LDDMM_LAUNCH(t.start, t.stop, k_pde_grad_m<T>, ft.blocks, dim3(ft.BX, ft.BY), 0, st, make_sl_geo<T>(g), m, static_cast<const T*>(nullptr), dv, T(0), T(0), static_cast<const T*>(nullptr), static_cast<T*>(nullptr), s);
 }
 
 template <typename T>
@@ -454,7 +455,8 @@ template void launch_compose<double>(const Grid&, const double*, const double*, 
   template void launch_pde_adjoint<T>(const Grid&, const T*, const T*, const T*, const T*, const T*, T*, double,   \
                                       hipStream_t, Profiler*);                                                  \
   template void launch_div<T>(const Grid&, const T*, T*, hipStream_t, Profiler*);                               \
-  template void launch_pde_lambda_grad<T>(const Grid&, const T*, const T*, double, T*, hipStream_t, Profiler*);  \
+  template void launch_pde_lambda_grad<T>(const Grid&, const T*, const T*, double, double, const T*, T*,         \
+                                          hipStream_t, Profiler*);                                              \
   template void launch_pde_source<T>(const Grid&, const T*, const T*, T*, hipStream_t, Profiler*);
 LDDMM_PDE_INST(float)
 LDDMM_PDE_INST(double)
