@@ -361,10 +361,11 @@ __global__ void __launch_bounds__(1024, (rt_plane_waves(sizeof(T), BIG))) k_plan
 
 // a / x: the hardware's FP32 reciprocal (1 ulp) and one correction of the quotient,
 // which rounds as the division it replaces does (to half an ulp but for rare ties) at
-// a third of its instructions; x >= 1 here.
+// a third of its instructions; x >= 1 here.  A power that overflowed (x infinite) gives
+// the division's 0: there the remainder x q would be infinity times 0.
 __device__ __forceinline__ float rt_div(float a, float x) {
   const float r = __builtin_amdgcn_rcpf(x), q = a * r;
-  return fmaf(fmaf(-x, q, a), r, q);
+  return __builtin_isinf(x) ? q : fmaf(fmaf(-x, q, a), r, q);
 }
 __device__ __forceinline__ double rt_div(double a, double x) { return a / x; }
 

@@ -85,3 +85,21 @@ def test_quotient_by_reciprocal_is_exact(tmp_path):
     subprocess.run([cc, "-O2", "-std=c++17", "-I", os.path.join(HERE, "native", "hip_host"), "-I",
                     os.path.join(ROOT, "paper_1807_04638_amd", "csrc"), str(src), "-o", exe], check=True)
     assert subprocess.run([exe]).returncode == 0
+
+
+# the highest frequencies' (1 + 0.0025 |k|^2)^s: beyond FP32's largest value for s = 80 (1e39), short of it for s = 70
+@pytest.mark.parametrize("s", [70, 80])
+@pytest.mark.parametrize("xs", [1, 2, 4])
+def test_inverse_symbol_beyond_the_largest_float_is_zero(exe, xs, s):
+    n = (6, 28, 50)
+    f = np.random.default_rng(5).standard_normal((1,) + n).astype(np.float32).astype(np.float64)
+    args = [*n, 1, xs, 16, 32, 1, s, 0, 0, 0, 1]
+    r = subprocess.run([exe] + [str(a) for a in args], input=f.tobytes(), capture_output=True, timeout=120)
+    assert r.returncode == 0, r.stderr.decode()[-2000:]
+    got = np.frombuffer(r.stdout).reshape(f.shape)
+    k2 = sum(np.meshgrid(*[np.fft.fftfreq(m, 1.0 / m) ** 2 for m in n], indexing="ij"))
+    with np.errstate(over="ignore"):
+        assert np.isinf(np.float32(1.0 + 0.0025 * k2.max()) ** np.float32(s)) == (s == 80)
+    ref = np.fft.ifftn(np.fft.fftn(f, axes=(1, 2, 3)) * (1.0 + 0.0025 * k2) ** -s, axes=(1, 2, 3)).real
+    # as above, and 2 s roundings of the power (of its base and its products)
+    assert np.linalg.norm(got - ref) <= 1.2e-7 * (8 * np.log2(np.prod(n)) + 2 * s) * np.linalg.norm(f)

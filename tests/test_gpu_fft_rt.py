@@ -8,6 +8,7 @@ import pytest
 import torch
 
 import oracle as O
+from paper_1807_04638_amd.lddmm import OP_K, apply_operator_noalloc
 from synth import random_field
 from test_gpu_parity import DTYPES, TOL, T, l_tol, make, rel, rounded, say
 
@@ -64,3 +65,19 @@ def test_addend_of_the_run_time_inverse_pass():
     g, _ = R.gradient(T(v0, dtype))
     assert rel(g, O.gradient(v0, I0, I1, p, lin)[0]) <= TOL[dtype]["grad"]
     assert rel(R.hessvec(T(dv, dtype)), O.hessvec(dv, lin, p)) <= TOL[dtype]["hv"]
+
+
+@pytest.mark.parametrize("split", [0, 1])
+@pytest.mark.parametrize("dtype", DTYPES)
+def test_inverse_symbol_beyond_the_largest_float(dtype, split):
+    """(1 + |k|^2)^13 reaches 966^13 = 6e38: K's coefficient there is 0 in FP32."""
+    n, s = (24, 28, 50), 13
+    R, p = make(n, dtype, alpha=1.0, s=s)
+    R.set_option("fft.force_split", split)
+    f = rounded(random_field(n, 7, kc=8.0), dtype)
+    ref = O.apply_K(f, p)
+    # rounding of about 2 log2(N) stages and of the power, on values of the input's size
+    tol = (1.2e-7 if dtype == torch.float32 else 2.3e-16) * (8 * np.log2(np.prod(n)) + 2 * s) * np.linalg.norm(f)
+    assert np.linalg.norm(R.apply_K(T(f, dtype)).double().cpu().numpy() - ref) <= tol
+    got = apply_operator_noalloc(OP_K, T(f, dtype), 1.0, s)
+    assert np.linalg.norm(got.double().cpu().numpy() - ref) <= tol
