@@ -1168,17 +1168,15 @@ int spectral_configure(SpectralPlan<T>& sp, const FftTuning& tune, std::string& 
   const int tb = tune.pencil_tb;
   const bool use_static = tune.use_static != 0;
   const bool walk = tune.plane_grid > 0;  // plane walk: compile-time plane kernels only
-  const size_t tables = size_t(H + H / 2 + 1) * cb + size_t(H + 1) * sizeof(int);
-  auto unit_lds = [&](int rows, int row_stride) { return size_t(rows) * row_stride * cb + size_t(rows) * cb + tables; };
+  const SpectralSizes z{n0, n1, H, cb, sp.max_lds};
   void* k[8] = {nullptr, nullptr, nullptr, nullptr, nullptr, nullptr, nullptr, nullptr};
   int nstatic = 0, plane_grid = 0;
   // units per plane: the plan's (half planes; quarters or thirds where a half does
-  // not fit the LDS), whole planes where asked for or with a plane walk
+  // not fit the LDS), whole planes where asked for, with a plane walk or where tiles
+  // of tb pencils leave no room for a group
   int xs = 1;
-  if (tune.plane_halves && !tune.force_split && !walk && sp.xs > 1 && tb % 2 == 0 &&
-      unit_lds(n1 / sp.xs, M) <= sp.max_lds)
-    xs = sp.xs;
-  const bool fused = xs > 1 || (!tune.force_split && unit_lds(n1, M) <= sp.max_lds);
+  if (tune.plane_halves && !tune.force_split && !walk && sp.xs > 1 && units_fit(z, sp.xs, tb)) xs = sp.xs;
+  const bool fused = xs > 1 || (!tune.force_split && units_fit(z, 1, tb));
   bool plane_rt = false, pencil_rt = false;
   size_t plane_lds = 0;
   int lm = M;
@@ -1200,7 +1198,7 @@ int spectral_configure(SpectralPlan<T>& sp, const FftTuning& tune, std::string& 
       if (k[KF_PLANE_FWD])
         plane_grid = walk && (sizeof(T) == 4 || tune.plane_threads != 1024) ? tune.plane_grid : 0;
     }
-    plane_lds = unit_lds(n1 / xs, M);
+    plane_lds = unit_lds(z, n1 / xs);
     if (k[KF_PLANE_FWD]) {
       nstatic++;
     } else {
@@ -1209,8 +1207,8 @@ int spectral_configure(SpectralPlan<T>& sp, const FftTuning& tune, std::string& 
       k[KF_PLANE_FWD] = (void*)rt_plane_fwd<T>(big);
       k[KF_PLANE_INV] = k[KF_PLANE_INV_ADD] = (void*)rt_plane_inv<T>(big);
       // an odd row stride (LDS banks) where it fits
-      if (unit_lds(n1 / xs, M | 1) <= sp.max_lds) lm = M | 1;
-      plane_lds = unit_lds(n1 / xs, lm);
+      if (unit_lds(z, n1 / xs, 1 - M % 2) <= sp.max_lds) lm = M | 1;
+      plane_lds = unit_lds(z, n1 / xs, lm - M);
     }
   }
   if (use_static && tune.pencil_threads == 256)
@@ -1223,10 +1221,8 @@ int spectral_configure(SpectralPlan<T>& sp, const FftTuning& tune, std::string& 
   }
   // groups of xs sequences per pencil workgroup; the pencils also keep a symbol
   // term per sequence
-  const int groups = tb / xs > 0 ? tb / xs : 1;
-  const size_t p0 = (size_t(n0) * groups * xs + n0) * cb + size_t(n0 + groups * xs) * sizeof(T);
-  const size_t p1 = (size_t(n1) * tb + n1) * cb + size_t(n1 + tb) * sizeof(T);
-  const size_t rl = size_t(tune.rows_rb) * M * cb + tables;
+  const size_t p0 = pencil_lds(z, n0, pencil_groups(tb, xs) * xs), p1 = pencil_lds(z, n1, tb);
+  const size_t rl = rows_lds(z, tune.rows_rb);
   if (p0 > sp.max_lds || (!fused && (p1 > sp.max_lds || rl > sp.max_lds))) {
     err = "transform tiles exceed the LDS of a workgroup";
     return LDDMM_EUNSUPPORTED;
@@ -1299,22 +1295,6 @@ int rt_plane_threads(size_t values) {
   return values * sizeof(cplx<T>) > 72 * 1024 ? 1024 : values > 1536 ? 512 : 256;
 }
 
-// Units that a plane is cut into (their tables are part of the plan): halves, or
-// quarters or thirds where a half does not fit the LDS; odd n1 gets thirds where
-// the whole plane does not fit.  1: whole planes only.
-template <typename T>
-int plane_units(int n1, int H, size_t max_lds) {
-  const size_t cb = sizeof(cplx<T>);
-  const size_t tables = size_t(H + H / 2 + 1) * cb + size_t(H + 1) * sizeof(int);
-  auto fits = [&](int xs) {
-    return n1 % xs == 0 && n1 / xs >= 4 && size_t(n1 / xs) * (H + 2) * cb + tables <= max_lds;
-  };
-  if (n1 % 2 != 0 && fits(1)) return 1;
-  for (int xs : {2, 4, 3})
-    if (fits(xs)) return xs;
-  return n1 % 2 == 0 && n1 >= 8 ? 2 : 1;
-}
-
 template <typename T>
 FftTuning default_tuning(const SpectralPlan<T>& sp) {
   FftTuning t;
@@ -1336,14 +1316,10 @@ FftTuning default_tuning(const SpectralPlan<T>& sp) {
   } else {
     t.plane_threads = rt_plane_threads<T>(size_t(sp.n1 / (sp.xs > 1 ? sp.xs : 1)) * sp.H);
   }
-  int tb = int(256 / cb);
-  while (tb > 1 && ((size_t(sp.n0) * tb + sp.n0) * cb + sp.n0 * sizeof(T) > sp.max_lds ||
-                    (size_t(sp.n1) * tb + sp.n1) * cb > sp.max_lds))
-    tb /= 2;
-  t.pencil_tb = tb;
-  const size_t tables = size_t(sp.H + sp.H / 2 + 1) * cb + size_t(sp.H + 1) * sizeof(int);
+  const SpectralSizes z{sp.n0, sp.n1, sp.H, cb, sp.max_lds};
+  t.pencil_tb = default_pencil_tb(z);
   int rb = 16;
-  while (rb > 1 && size_t(rb) * sp.M * cb + tables > sp.max_lds) rb /= 2;
+  while (rb > 1 && rows_lds(z, rb) > sp.max_lds) rb /= 2;
   t.rows_rb = rb;
   t.force_split = 0;
   t.use_static = 1;
@@ -1371,7 +1347,8 @@ int spectral_plan_tables(SpectralPlan<T>& sp, const int n[3], size_t max_lds, bo
     return LDDMM_EUNSUPPORTED;
   }
   const int H = sp.H, M = sp.M;
-  sp.xs = units ? plane_units<T>(n[1], H, max_lds) : 1;
+  const SpectralSizes z{n[0], n[1], H, sizeof(cplx<T>), max_lds};
+  sp.xs = units ? plane_units(z) : 1;
   if (sp.xs > 1 && !make_plan(n[1] / sp.xs, sp.p1u)) sp.xs = 1;
   // Axes that no compile-time kernel transforms take the run-time kernels' plans of
   // the fewest stages: one exchange through the LDS and one barrier less where 2 5 5
@@ -1540,7 +1517,7 @@ void spectral_apply(const SpectralPlan<T>& sp, const T* in, T* out, int ncomp, d
   const int P = sp.n1 * sp.M;
   const T scale = T(out_scale / (double(sp.n0) * sp.n1 * sp.n2));  // the inverse's 1/N and the caller's factor
   // x0 pencils: groups of the xs sequences that share a slot of the units' spectra
-  const int groups = tu.pencil_tb / xs > 0 ? tu.pencil_tb / xs : 1, nin = P / xs, hs = xs > 1 ? nin : 0;
+  const int groups = pencil_groups(tu.pencil_tb, xs), nin = P / xs, hs = xs > 1 ? nin : 0;
   const dim3 g0((nin + groups - 1) / groups, ncomp);
   const long long c = sizeof(cplx<T>);
   // neighbouring pencil tiles share cache lines unless every tile's run starts on a

@@ -9,10 +9,64 @@
 // planes.
 #pragma once
 
+#include <cstddef>
+#include <initializer_list>
+
 #include "fft_core.h"
 #include "index_math.h"
 
 namespace lddmm {
+
+// Host: what decides the launch shapes of a grid's transforms.
+struct SpectralSizes {
+  int n0, n1, H;   // H = n2 / 2
+  size_t cb;       // bytes of a complex value
+  size_t max_lds;  // of a workgroup
+};
+
+// LDS of the split path's row kernels for rb rows, with the x2 tables.
+inline size_t rows_lds(const SpectralSizes& z, int rb) {
+  return size_t(rb) * (z.H + 1) * z.cb + size_t(z.H + z.H / 2 + 1) * z.cb + size_t(z.H + 1) * sizeof(int);
+}
+// LDS of a plane kernel for `rows` x1 rows at a row stride of H + 1 + `pad` values.
+inline size_t unit_lds(const SpectralSizes& z, int rows, int pad = 0) {
+  return rows_lds(z, rows) + size_t(rows) * (pad + 1) * z.cb;
+}
+// LDS of a pencil kernel for `seqs` sequences of n values, with a symbol term for each.
+inline size_t pencil_lds(const SpectralSizes& z, int n, int seqs) {
+  return (size_t(n) * seqs + n) * z.cb + size_t(n + seqs) * (z.cb / 2);
+}
+// Groups of xs sequences per x0 pencil workgroup at a tile of tb pencils.
+inline int pencil_groups(int tb, int xs) { return tb / xs > 0 ? tb / xs : 1; }
+
+// Pencils per workgroup by default: 256-byte rows, fewer on axes that do not fit the LDS.
+inline int default_pencil_tb(const SpectralSizes& z) {
+  int tb = int(256 / z.cb);
+  while (tb > 1 && ((size_t(z.n0) * tb + z.n0) * z.cb + z.n0 * (z.cb / 2) > z.max_lds ||
+                    (size_t(z.n1) * tb + z.n1) * z.cb > z.max_lds))
+    tb /= 2;
+  return tb;
+}
+
+// True if planes in xs units (1: whole) can run with pencil tiles of tb: a unit fits the
+// LDS, and so do the pencils of a group of xs, which may be more than tb.
+inline bool units_fit(const SpectralSizes& z, int xs, int tb) {
+  if (unit_lds(z, z.n1 / xs) > z.max_lds) return false;
+  if (xs == 1) return true;
+  return z.n1 % xs == 0 && z.n1 / xs >= 4 && tb % 2 == 0 &&
+         pencil_lds(z, z.n0, pencil_groups(tb, xs) * xs) <= z.max_lds;
+}
+
+// Units that a plane is cut into (their tables are part of the plan): halves, or
+// quarters or thirds where halves do not fit; odd n1 gets thirds where the whole plane
+// does not fit.  1: whole planes, or the split path where those do not fit.
+inline int plane_units(const SpectralSizes& z) {
+  const int tb = default_pencil_tb(z);
+  if (z.n1 % 2 != 0 && units_fit(z, 1, tb)) return 1;
+  for (int xs : {2, 4, 3})
+    if (units_fit(z, xs, tb)) return xs;
+  return z.n1 % 2 == 0 && z.n1 >= 8 ? 2 : 1;
+}
 
 // One stage of a run-time plan with what its kernels would otherwise divide for.
 struct RtStage {

@@ -81,3 +81,14 @@ def test_inverse_symbol_beyond_the_largest_float(dtype, split):
     assert np.linalg.norm(R.apply_K(T(f, dtype)).double().cpu().numpy() - ref) <= tol
     got = apply_operator_noalloc(OP_K, T(f, dtype), 1.0, s)
     assert np.linalg.norm(got.double().cpu().numpy() - ref) <= tol
+
+
+def test_long_axis_whose_pencils_leave_no_room_for_a_cut():
+    """2304 x 2625 x 4 FP64: planes fit the LDS in thirds, but three sequences of 2304
+    values beside their tables do not; two do, on the split path."""
+    n, dtype = (2304, 2625, 4), torch.float64
+    R, p = make(n, dtype, nt=1, alpha=0.0025)
+    assert (R.get_option("fft.plane_halves_used"), R.get_option("fft.fused")) == (0, 0)
+    f = np.random.default_rng(3).standard_normal(n)
+    assert rel(R.apply_K(T(f, dtype)), O.apply_K(f, p)) <= TOL[dtype]["op"]
+    R.close()
