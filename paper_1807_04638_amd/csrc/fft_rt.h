@@ -65,7 +65,7 @@ inline int plane_units(const SpectralSizes& z) {
   if (z.n1 % 2 != 0 && units_fit(z, 1, tb)) return 1;
   for (int xs : {2, 4, 3})
     if (units_fit(z, xs, tb)) return xs;
-  return z.n1 % 2 == 0 && z.n1 >= 8 ? 2 : 1;
+  return 1;
 }
 
 // One stage of a run-time plan with what its kernels would otherwise divide for.

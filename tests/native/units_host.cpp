@@ -17,6 +17,7 @@ static bool uncut_runs(const SpectralSizes& z, int tb) {
 static int check(const SpectralSizes& z, int want = 0) {
   const int xs = plane_units(z);
   if (want && (units_fit(z, xs, default_pencil_tb(z)) ? xs : 1) != want) return 1;
+  if (xs > 1 && !units_fit(z, xs, default_pencil_tb(z))) return 4;  // planned as cut, runs whole or split
   for (int tb : {default_pencil_tb(z), 1, 2, 4, 6, 8, 16, 32}) {
     if (xs == 1 || !units_fit(z, xs, tb)) continue;  // runs uncut
     if (z.n1 % xs || unit_lds(z, z.n1 / xs) > z.max_lds) return 2;

@@ -92,3 +92,29 @@ def test_long_axis_whose_pencils_leave_no_room_for_a_cut():
     f = np.random.default_rng(3).standard_normal(n)
     assert rel(R.apply_K(T(f, dtype)), O.apply_K(f, p)) <= TOL[dtype]["op"]
     R.close()
+
+
+def operators_match(R, p, n, dtype):
+    f = rounded(random_field(n, 31, kc=max(n) / 4), dtype)
+    Lf = O.apply_L(f, p)
+    assert rel(R.apply_K(T(f, dtype)), O.apply_K(f, p)) <= TOL[dtype]["op"]
+    assert rel(R.apply_L(T(f, dtype)), Lf) <= l_tol(p, f, Lf, dtype)
+
+
+# planes whose stages have radices 6, 9, 10, 12, 14 and 15, on the split path's kernels
+@pytest.mark.parametrize("n", [(50, 96, 100), (54, 36, 60), (6, 210, 240), (7, 224, 252)])
+@pytest.mark.parametrize("dtype", DTYPES)
+def test_radices_on_the_split_path(n, dtype):
+    R, p = make(n, dtype, alpha=0.0025)
+    R.set_option("fft.force_split", 1)
+    assert R.get_option("fft.fused") == 0
+    operators_match(R, p, n, dtype)
+
+
+def test_split_grids_keep_the_compile_time_rows():
+    """16 x 490 x 180 FP32: no unit of the planes fits the LDS; rows of 180 and pencils
+    of 16 points have compile-time kernels."""
+    n, dtype = (16, 490, 180), torch.float32
+    R, p = make(n, dtype, alpha=0.0025)
+    assert (R.get_option("fft.fused"), R.get_option("fft.static_kernels")) == (0, 2)
+    operators_match(R, p, n, dtype)
