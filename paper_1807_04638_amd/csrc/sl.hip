@@ -90,29 +90,52 @@ __device__ __forceinline__ void load_pair(const float* __restrict__ f, int o, fl
   hi = v.y;
 }
 
-// FP32 reads each x2 pair with one load (half the gathers); FP64 reads the
-// corners one by one (its 16-byte pairs measured slower than two loads).  At the end
-// of a row the pair before it holds the lower corner, and only the upper one takes a
-// load of its own.
-template <typename T>
-__device__ __forceinline__ T tri_eval(const Tri<T>& tr, const T* __restrict__ f) {
-  T acc = T(0);
+// Values of NC fields at the point.  FP32 reads each x2 pair with one load (half the
+// gathers); at the end of a row the pair before it holds the lower corner, and only the
+// upper one takes a load of its own.  All pairs' loads come first, so that they are in
+// flight together and the row ends cost one branch (a step at 128^3 38 us, with a branch
+// per pair 46).  FP64 reads the corners one by one, field by field (16-byte pairs
+// measured slower than two loads, and all fields' loads first no faster).
+template <typename T, int NC>
+__device__ __forceinline__ void tri_eval(T (&out)[NC], const Tri<T>& tr, const T* const* f) {
+  if constexpr (sizeof(T) == 4) {
+    T lo[NC][4], hi[NC][4];
 #pragma unroll
-  for (int k = 0; k < 4; ++k) {
-    T lo, hi;
-    if constexpr (sizeof(T) == 4) {
-      load_pair(f, tr.wrap ? tr.o[k] - 1 : tr.o[k], lo, hi);
-      if (tr.wrap) {
-        lo = hi;
-        hi = f[tr.o[k] - tr.n2m1];
-      }
-    } else {
-      lo = f[tr.o[k]];
-      hi = f[tr.wrap ? tr.o[k] - tr.n2m1 : tr.o[k] + 1];
+    for (int c = 0; c < NC; ++c)
+#pragma unroll
+      for (int k = 0; k < 4; ++k) load_pair(f[c], tr.wrap ? tr.o[k] - 1 : tr.o[k], lo[c][k], hi[c][k]);
+    if (tr.wrap) {
+#pragma unroll
+      for (int c = 0; c < NC; ++c)
+#pragma unroll
+        for (int k = 0; k < 4; ++k) {
+          lo[c][k] = hi[c][k];
+          hi[c][k] = f[c][tr.o[k] - tr.n2m1];
+        }
     }
-    acc += tr.w01[k] * (lo + tr.t2 * (hi - lo));
+#pragma unroll
+    for (int c = 0; c < NC; ++c) {
+      out[c] = T(0);
+#pragma unroll
+      for (int k = 0; k < 4; ++k) out[c] += tr.w01[k] * (lo[c][k] + tr.t2 * (hi[c][k] - lo[c][k]));
+    }
+  } else {
+#pragma unroll
+    for (int c = 0; c < NC; ++c) {
+      out[c] = T(0);
+#pragma unroll
+      for (int k = 0; k < 4; ++k) {
+        const T lo = f[c][tr.o[k]], hi = f[c][tr.wrap ? tr.o[k] - tr.n2m1 : tr.o[k] + 1];
+        out[c] += tr.w01[k] * (lo + tr.t2 * (hi - lo));
+      }
+    }
   }
-  return acc;
+}
+template <typename T>
+__device__ __forceinline__ T tri_one(const Tri<T>& tr, const T* f) {
+  T v[1];
+  tri_eval<T, 1>(v, tr, &f);
+  return v[0];
 }
 
 // ---------------------------------------------------------------------------
@@ -127,14 +150,25 @@ __device__ __forceinline__ T tri_eval(const Tri<T>& tr, const T* __restrict__ f)
 // SL_ADJOINT  lam_old = lam_new(Y) exp(dt/2 (D_old(x) + D_new(Y))), forward, D = div v
 //
 // Bound by the L1's return path when gathered from global memory (24 8-byte gathers
-// per voxel, texture data unit 98 % busy: 52 us at 128^3 FP32 for 100 MB).  A step
-// moves a point by less than a voxel as a rule, so the workgroup puts its tile of
-// each field with one voxel around it into the LDS (1.5 to 2.3 times the tile's
-// values, coalesced) and gathers there, without wrapping: 32 us.  A tile with a
-// longer displacement gathers from global memory.  The second fields' window is in
-// flight in registers while the first is gathered.
+// per voxel: 38 us at 128^3 FP32 for 100 MB).  A step moves a point by less than a
+// voxel as a rule, so the workgroup puts its tile of each field with one voxel around
+// it into the LDS (2 planes of 4 x 64 voxels: 3.1 times the tile's values, of 8 x 32:
+// 2.7; coalesced) and gathers there, without wrapping.  The second fields' window is in
+// flight in registers while the first is gathered.  Lanes whose point leaves the window
+// gather from global memory, and so does the whole tile, before it loads a window, where
+// points leave it in many of its waves.  us per sl_step with steps of at most 0.5, 1.5,
+// 3 and 6 voxels, in brackets all gathering (k_sl_points): 128^3 FP32 28, 27, 43, 52
+// (38, 38, 41, 49), FP64 44, 44, 58, 74 (55, 55, 56, 74).
 // ---------------------------------------------------------------------------
 enum { SL_START, SL_STEP, SL_STATE, SL_INCR, SL_ADJOINT };
+constexpr int sl_fields(int kind) { return kind == SL_START ? 0 : kind == SL_STEP ? 3 : kind == SL_STATE ? 1 : 2; }
+
+// Waves with a point outside the window, per plane of a tile's four, above which the
+// tile gathers from global memory.  FP32 one (128^3, 2 voxels a step: 33.8 us, none 36.5,
+// two 33.2; 96^3, 1.5 voxels: 17.3, 17.4, 18.9); FP64 none (60 x 84 x 70, 1.5 voxels:
+// 13.4 us, one 16.3): its lone lanes' loads are serial.
+template <typename T>
+constexpr int kSlSpread = sizeof(T) == 4 ? 1 : 0;
 
 template <typename T>
 struct SlIo {
@@ -145,22 +179,23 @@ struct SlIo {
   T* out;
 };
 
-// Window elements of a lane, NF fields: registers <- global, LDS <- registers.
+// Window elements of a lane, NF fields: registers <- global, LDS <- registers.  Lanes past
+// the window's end load its last element again: a load behind a branch each would wait
+// for the one before it.
 template <typename T, int NF, int NL>
 __device__ __forceinline__ void window_load(T (&r)[NF][NL], const T* const (&f)[3], const int (&go)[NL]) {
 #pragma unroll
   for (int c = 0; c < NF; ++c)
 #pragma unroll
-    for (int l = 0; l < NL; ++l)
-      if (go[l] >= 0) r[c][l] = f[c][go[l]];
+    for (int l = 0; l < NL; ++l) r[c][l] = f[c][go[l]];
 }
 template <typename T, int NF, int NL>
-__device__ __forceinline__ void window_store(T* w, const T (&r)[NF][NL], const int (&go)[NL], int count) {
+__device__ __forceinline__ void window_store(T* w, const T (&r)[NF][NL], int count) {
 #pragma unroll
   for (int c = 0; c < NF; ++c)
 #pragma unroll
     for (int l = 0; l < NL; ++l)
-      if (go[l] >= 0) w[c * count + int(threadIdx.x) + l * kSlLanes] = r[c][l];
+      if (int(threadIdx.x) + l * kSlLanes < count) w[c * count + int(threadIdx.x) + l * kSlLanes] = r[c][l];
 }
 
 // Cell and weights of a displacement of less than a voxel in a window: lower corner
@@ -201,68 +236,141 @@ __device__ __forceinline__ T win_eval(const WinTri<T>& w, const T* win, const Sl
   return acc;
 }
 
+// Result of a step at voxel o: disp and the fields' values there.
+template <typename T, int KIND, int NR>
+__device__ __forceinline__ void sl_write(const SlGeo<T>& g, const SlIo<T>& io, int o, const T (&d)[3], const T (&v)[NR],
+                                         T dt) {
+  if constexpr (KIND == SL_START || KIND == SL_STEP) {
+#pragma unroll
+    for (int c = 0; c < 3; ++c) io.out[c * g.N + o] = KIND == SL_STEP ? v[KIND == SL_STEP ? c : 0] + d[c] : d[c];
+  } else if constexpr (KIND == SL_STATE) {
+    io.out[o] = v[0];
+  } else if constexpr (KIND == SL_INCR) {
+    io.out[o] = v[0] + T(0.5) * dt * (v[NR - 1] + io.at_x[o]);
+  } else {
+    io.out[o] = v[0] * exp(T(0.5) * dt * (io.at_x[o] + v[NR - 1]));
+  }
+}
+
+// A voxel's step by gathers from global memory, vc its velocity (not written where !own).
+template <typename T, int KIND>
+__device__ __forceinline__ void sl_point(const SlGeo<T>& g, const SlIo<T>& io, int i0, int i1, int i2, const T (&vc)[3],
+                                         T dt, bool own) {
+  constexpr int NF = sl_fields(KIND), NR = NF > 0 ? NF : 1;
+  constexpr T sgn = KIND == SL_ADJOINT ? T(1) : T(-1);
+  const T* const vg[3] = {io.vg, io.vg + g.N, io.vg + 2 * g.N};
+  T d[3], v[NR] = {};
+  tri_eval<T, 3>(d, tri_setup(g, i0, i1, i2, sgn * dt * vc[0] * g.invh[0], sgn * dt * vc[1] * g.invh[1],
+                              sgn * dt * vc[2] * g.invh[2]),
+                 vg);
+#pragma unroll
+  for (int c = 0; c < 3; ++c) d[c] = sgn * T(0.5) * dt * (vc[c] + d[c]);
+  if constexpr (NF > 0)
+    tri_eval<T, NF>(v, tri_setup(g, i0, i1, i2, d[0] * g.invh[0], d[1] * g.invh[1], d[2] * g.invh[2]), io.f);
+  if (own) sl_write<T, KIND, NR>(g, io, (i0 * g.n1 + i1) * g.n2 + i2, d, v, dt);
+}
+
+template <typename T, int KIND>
+__global__ void __launch_bounds__(256) k_sl_points(SlGeo<T> g, SlIo<T> io, T dt) {
+  int i0, i1, i2;
+  if (!tile_voxel(g.ft, g.n1, g.n2, i0, i1, i2)) return;
+  const int o = (i0 * g.n1 + i1) * g.n2 + i2;
+  const T vc[3] = {io.vc[o], io.vc[g.N + o], io.vc[2 * g.N + o]};
+  sl_point<T, KIND>(g, io, i0, i1, i2, vc, dt, true);
+}
+
+// FP32 held to 128 registers (128^3 PDE steps 24 us, unbounded 26); FP64 needs no more
+// than that by itself, and under a bound waits for the gathers one by one (6 voxels a
+// step: 74 us, bounded 82).
 template <typename T, int KIND, int T0>
-__global__ void __launch_bounds__(kSlLanes) k_sl(SlGeo<T> g, SlTile t, SlIo<T> io, T dt) {
-  constexpr int NF = KIND == SL_START ? 0 : KIND == SL_STEP ? 3 : KIND == SL_STATE ? 1 : 2;
+__global__ void __launch_bounds__(kSlLanes, sizeof(T) == 4 ? 4 : 1) k_sl(SlGeo<T> g, SlTile t, SlIo<T> io, T dt) {
+  constexpr int NF = sl_fields(KIND), NR = NF > 0 ? NF : 1;
   constexpr int NL = sl_window_loads(T0);
+  constexpr T sgn = KIND == SL_ADJOINT ? T(1) : T(-1);
   extern __shared__ __align__(16) unsigned char smem[];
+  __shared__ int votes[kSlLanes / 64];
   T* win = reinterpret_cast<T*>(smem);
   int b0, b1, b2;
   if (!sl_tile_block(t, int(blockIdx.x), b0, b1, b2)) return;
   const int lane = int(threadIdx.x);
-  int go[NL];  // grid offsets of the lane's window elements (-1: none)
-#pragma unroll
-  for (int l = 0; l < NL; ++l) {
-    const int e = lane + l * kSlLanes;
-    const int w0 = index_quot(e, t.inv_plane), r = e - mul24(w0, t.plane);
-    const int w1 = index_quot(r, t.inv_row), w2 = r - mul24(w1, t.row);
-    go[l] = e < t.count ? (sl_tile_wrap(b0, w0, g.n0) * g.n1 + sl_tile_wrap(b1, w1, g.n1)) * g.n2 +
-                              sl_tile_wrap(b2, w2, g.n2)
-                        : -1;
-  }
   const T* const vg[3] = {io.vg, io.vg + g.N, io.vg + 2 * g.N};
-  T rv[3][NL];
-  window_load<T, 3, NL>(rv, vg, go);
   const int l1 = index_quot(lane, t.inv_T2), l2 = lane - mul24(l1, t.T2);
   const int i1 = b1 + l1, i2 = b2 + l2;
   const bool column = l1 < t.T1 && i1 < g.n1 && i2 < g.n2;
   const int s0 = g.n1 * g.n2, o0 = (b0 * g.n1 + i1) * g.n2 + i2;
   const int centre = t.plane + (l1 + 1) * t.row + l2 + 1;
-  constexpr T sgn = KIND == SL_ADJOINT ? T(1) : T(-1);
   T d[T0][3];  // vc, then the displacement
   WinTri<T> w[T0];
-  bool near = true;
+  unsigned far = 0;  // planes whose point leaves the window
+#pragma unroll
+  for (int k = 0; k < T0; ++k)
+#pragma unroll
+    for (int c = 0; c < 3; ++c) d[k][c] = column && b0 + k < g.n0 ? io.vc[c * g.N + o0 + k * s0] : T(0);
+  int spread = 0;
 #pragma unroll
   for (int k = 0; k < T0; ++k) {
-    const bool on = column && b0 + k < g.n0;
     T p[3];
 #pragma unroll
-    for (int c = 0; c < 3; ++c) {
-      d[k][c] = on ? io.vc[c * g.N + o0 + k * s0] : T(0);
-      p[c] = sgn * dt * d[k][c] * g.invh[c];
-    }
-    near = win_setup(w[k], p, centre + k * t.plane, t) && near;
+    for (int c = 0; c < 3; ++c) p[c] = sgn * dt * d[k][c] * g.invh[c];
+    const bool out = !win_setup(w[k], p, centre + k * t.plane, t);
+    far |= out ? 1u << k : 0u;
+    spread += __any(out) ? 1 : 0;
   }
-  window_store<T, 3, NL>(win, rv, go, t.count);
-  const bool near_p = !__syncthreads_or(!near);
-  constexpr int NR = NF > 0 ? NF : 1;
+  if ((lane & 63) == 0) votes[lane >> 6] = spread;
+  __syncthreads();
+  spread = 0;
+#pragma unroll
+  for (int i = 0; i < kSlLanes / 64; ++i) spread += votes[i];
+  if (__builtin_amdgcn_readfirstlane(spread) > kSlSpread<T> * T0) {
+    const int j1 = i1 < g.n1 ? i1 : 0, j2 = i2 < g.n2 ? i2 : 0;  // lanes without a voxel gather at another
+#pragma unroll 1
+    for (int k = 0; k < T0 && b0 + k < g.n0; ++k) {
+      T vc[3];
+#pragma unroll
+      for (int c = 0; c < 3; ++c) {
+        if constexpr (T0 > 2) {  // from memory again: the choice among four planes' registers spills
+          vc[c] = io.vc[c * g.N + ((b0 + k) * g.n1 + j1) * g.n2 + j2];
+        } else {
+          vc[c] = d[0][c];
+#pragma unroll
+          for (int m = 1; m < T0; ++m) vc[c] = k == m ? d[m][c] : vc[c];
+        }
+      }
+      sl_point<T, KIND>(g, io, b0 + k, j1, j2, vc, dt, column);
+    }
+    return;
+  }
+  int go[NL];  // grid offsets of the lane's window elements
+#pragma unroll
+  for (int l = 0; l < NL; ++l) {
+    const int e = min(lane + l * kSlLanes, t.count - 1);
+    const int w0 = index_quot(e, t.inv_plane), r = e - mul24(w0, t.plane);
+    const int w1 = index_quot(r, t.inv_row), w2 = r - mul24(w1, t.row);
+    go[l] = (sl_tile_wrap(b0, w0, g.n0) * g.n1 + sl_tile_wrap(b1, w1, g.n1)) * g.n2 + sl_tile_wrap(b2, w2, g.n2);
+  }
+  T rv[3][NL];
+  window_load<T, 3, NL>(rv, vg, go);
+  window_store<T, 3, NL>(win, rv, t.count);
+  __syncthreads();
   T rf[NR][NL];
   if constexpr (NF > 0) window_load<T, NF, NL>(rf, io.f, go);
-  near = true;
 #pragma unroll
   for (int k = 0; k < T0; ++k) {
     const bool on = column && b0 + k < g.n0;
     T v[3] = {T(0), T(0), T(0)};
-    if (near_p) {
-      if (column) {
-#pragma unroll
-        for (int c = 0; c < 3; ++c) v[c] = win_eval(w[k], win + c * t.count, t);
-      }
-    } else if (on) {
+    if (far >> k & 1) {  // only where the lane is on
       const Tri<T> tp = tri_setup(g, b0 + k, i1, i2, sgn * dt * d[k][0] * g.invh[0], sgn * dt * d[k][1] * g.invh[1],
                                   sgn * dt * d[k][2] * g.invh[2]);
 #pragma unroll
-      for (int c = 0; c < 3; ++c) v[c] = tri_eval(tp, vg[c]);
+      for (int c = 0; c < 3; ++c) {
+        v[c] = tri_one(tp, vg[c]);
+        // the fields' corners one after another (FP64 with one or two fields: all at once
+        // pass 128 registers; with three they do not)
+        if constexpr (NF < 3) __builtin_amdgcn_sched_barrier(0);
+      }
+    } else if (column) {
+#pragma unroll
+      for (int c = 0; c < 3; ++c) v[c] = win_eval(w[k], win + c * t.count, t);
     }
     T p[3];
 #pragma unroll
@@ -270,37 +378,32 @@ __global__ void __launch_bounds__(kSlLanes) k_sl(SlGeo<T> g, SlTile t, SlIo<T> i
       d[k][c] = on ? sgn * T(0.5) * dt * (d[k][c] + v[c]) : T(0);
       p[c] = d[k][c] * g.invh[c];
     }
-    if constexpr (NF > 0) near = win_setup(w[k], p, centre + k * t.plane, t) && near;
+    if constexpr (NF > 0) {
+      const unsigned bit = 1u << k;
+      far = win_setup(w[k], p, centre + k * t.plane, t) ? far & ~bit : far | bit;
+    }
   }
-  bool near_x = true;
   if constexpr (NF > 0) {
-    near_x = !__syncthreads_or(!near);  // and the first window has been read
-    window_store<T, NF, NL>(win, rf, go, t.count);
+    __syncthreads();  // the first window has been read
+    window_store<T, NF, NL>(win, rf, t.count);
     __syncthreads();
   }
 #pragma unroll
   for (int k = 0; k < T0; ++k) {
     if (!(column && b0 + k < g.n0)) continue;
     T v[NR] = {};
-    if (near_x) {
+    if constexpr (NF > 0) {
+      if (far >> k & 1) {
+        const Tri<T> tx =
+            tri_setup(g, b0 + k, i1, i2, d[k][0] * g.invh[0], d[k][1] * g.invh[1], d[k][2] * g.invh[2]);
 #pragma unroll
-      for (int c = 0; c < NF; ++c) v[c] = win_eval(w[k], win + c * t.count, t);
-    } else {
-      const Tri<T> tx = tri_setup(g, b0 + k, i1, i2, d[k][0] * g.invh[0], d[k][1] * g.invh[1], d[k][2] * g.invh[2]);
+        for (int c = 0; c < NF; ++c) v[c] = tri_one(tx, io.f[c]);
+      } else {
 #pragma unroll
-      for (int c = 0; c < NF; ++c) v[c] = tri_eval(tx, io.f[c]);
+        for (int c = 0; c < NF; ++c) v[c] = win_eval(w[k], win + c * t.count, t);
+      }
     }
-    const int o = o0 + k * s0;
-    if constexpr (KIND == SL_START || KIND == SL_STEP) {
-#pragma unroll
-      for (int c = 0; c < 3; ++c) io.out[c * g.N + o] = KIND == SL_STEP ? v[KIND == SL_STEP ? c : 0] + d[k][c] : d[k][c];
-    } else if constexpr (KIND == SL_STATE) {
-      io.out[o] = v[0];
-    } else if constexpr (KIND == SL_INCR) {
-      io.out[o] = v[0] + T(0.5) * dt * (v[NR - 1] + io.at_x[o]);
-    } else {
-      io.out[o] = v[0] * exp(T(0.5) * dt * (io.at_x[o] + v[NR - 1]));
-    }
+    sl_write<T, KIND, NR>(g, io, o0 + k * s0, d[k], v, dt);
   }
 }
 
@@ -311,7 +414,7 @@ __global__ void __launch_bounds__(256)
   if (!tile_voxel(g.ft, g.n1, g.n2, i0, i1, i2)) return;
   const int o = (i0 * g.n1 + i1) * g.n2 + i2;
   const Tri<T> t = tri_setup(g, i0, i1, i2, u[o] * g.invh[0], u[g.N + o] * g.invh[1], u[2 * g.N + o] * g.invh[2]);
-  J[o] = tri_eval(t, I);
+  J[o] = tri_one(t, I);
 }
 
 // D = div_h v (central differences)
@@ -356,28 +459,30 @@ __global__ void __launch_bounds__(256)
 
 namespace {
 
-// Planes per tile: the more, the fewer window values per voxel (1.9, 2.3, 3.5 times
-// the tile's for 4, 2, 1 planes of 8 x 32 voxels); halved until at least 1024
-// workgroups share the 256 compute units.  us per sl_step with 4, 2, 1 planes: 128^3
-// FP32 31.9, 36.3, 39.9 (52 by gathers from global memory); 64^3 FP32 10.6, 8.9, 8.9
-// (10.2); 32^3 FP32 10.0, 7.5, 6.1 (9.2).  FP64 stops at 2 (128^3: 63, 54, 83; 80 by
-// gathers): four planes' registers leave two waves per SIMD.
+// Windows where the tiles give each compute unit one and a half workgroups or more, plain
+// gathers below.  us per sl_step by gathers / by windows: FP32 32^3 (128 tiles) 4.2 / 6.0,
+// 48^3 (240) 6.0 / 6.3, 64^3 (512) 7.9 / 6.9, 60 x 84 x 70 (720) 11.0 / 10.7; FP64, twice
+// the bytes and registers, 48^3 7.3 / 8.7, 64^3 9.6 / 10.2, 60 x 84 x 70 17.2 / 13.5.
+// Tiles of two planes.  Of four in FP32 from 16384 tiles on (216^3 has 24192): 2.3 window
+// values per voxel instead of 3.1, where the fields no longer stay in the caches (256^3:
+// sl_step 196 us, two planes 212; 200^3, 16000 tiles, 97 either way), though gathers then
+// run in fewer waves (3 voxels a step: 350, 336); not the steps of two fields (197, 183).
 template <typename T, int KIND>
 void launch_sl(const char* name, const Grid& g, const SlIo<T>& io, double dt, hipStream_t st, Profiler* prof) {
   KernelTimer timer(prof, name);
-  SlTile t = sl_tile(g.n0, g.n1, g.n2, sizeof(T) == 4 ? 4 : 2);
-  while (t.T0 > 1 && t.blocks < 1024) t = sl_tile(g.n0, g.n1, g.n2, t.T0 / 2);
-  const size_t lds = size_t(3) * t.count * sizeof(T);
   const SlGeo<T> geo = make_sl_geo<T>(g);
-  if constexpr (sizeof(T) == 4)
-    if (t.T0 == 4) {
-      LDDMM_LAUNCH(timer.start, timer.stop, (k_sl<T, KIND, 4>), t.blocks, kSlLanes, lds, st, geo, t, io, T(dt));
+  SlTile t = sl_tile(g.n0, g.n1, g.n2, 2);
+  if (t.blocks < (sizeof(T) == 4 ? 400u : 600u)) {
+    LDDMM_LAUNCH(timer.start, timer.stop, (k_sl_points<T, KIND>), geo.ft.blocks, dim3(geo.ft.BX, geo.ft.BY), 0, st, geo, io, T(dt));
+    return;
+  }
+  if constexpr (sizeof(T) == 4 && sl_fields(KIND) != 2)
+    if (t.blocks >= 16384) {
+      t = sl_tile(g.n0, g.n1, g.n2, 4);
+      LDDMM_LAUNCH(timer.start, timer.stop, (k_sl<T, KIND, 4>), t.blocks, kSlLanes, size_t(3) * t.count * sizeof(T), st, geo, t, io, T(dt));
       return;
     }
-  if (t.T0 == 2)
-    LDDMM_LAUNCH(timer.start, timer.stop, (k_sl<T, KIND, 2>), t.blocks, kSlLanes, lds, st, geo, t, io, T(dt));
-  else
-    LDDMM_LAUNCH(timer.start, timer.stop, (k_sl<T, KIND, 1>), t.blocks, kSlLanes, lds, st, geo, t, io, T(dt));
+  LDDMM_LAUNCH(timer.start, timer.stop, (k_sl<T, KIND, 2>), t.blocks, kSlLanes, size_t(3) * t.count * sizeof(T), st, geo, t, io, T(dt));
 }
 
 }  // namespace
