@@ -68,6 +68,18 @@ inline int plane_units(const SpectralSizes& z) {
   return 1;
 }
 
+// Vector fields of a stack of `count` that one spectral pass takes: spectra (`one` bytes a
+// field) within 96 MB, at most 256, and no more than the split path's x1 pencils can
+// launch (three rows of n0 workgroups a field; a grid's second dimension ends at 65536).
+inline int fields_per_pass(size_t one, int count, int n0) {
+  const size_t most = size_t(96) << 20;
+  size_t k = one > 0 ? most / one : 1;
+  if (k > size_t(count)) k = size_t(count);
+  if (k > 256) k = 256;
+  if (k > size_t(65536 / (3 * n0))) k = size_t(65536 / (3 * n0));
+  return k < 1 ? 1 : int(k);
+}
+
 // One stage of a run-time plan with what its kernels would otherwise divide for.
 struct RtStage {
   int R;      // radix

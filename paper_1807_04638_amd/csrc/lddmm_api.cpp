@@ -1516,7 +1516,7 @@ class Engine {
     // passes of 16 us, now 2 of 54; 128^3 33 of 38, now 8 of 86.  Their spectra stay within
     // a share of the 256 MB cache; without memory for them one field at a time.
     const size_t one = spectrum_bytes(sp, 3);
-    pbatch = int(std::min<size_t>({size_t(96) << 20, one * (P.nt + 1), one * 256}) / one);
+    pbatch = fields_per_pass(one, P.nt + 1, g.n0);
     if (pbatch > 1) {
       T* q = nullptr;
       if (alloc(&q, (long long)(pbatch * one / sizeof(T)))) {
@@ -1525,7 +1525,6 @@ class Engine {
       }
       pspec = reinterpret_cast<cplx<T>*>(q);
     }
-    if (pbatch < 1) pbatch = 1;
     pde_ready = true;
     return 0;
   }

@@ -26,6 +26,17 @@ static int check(const SpectralSizes& z, int want = 0) {
   return 0;
 }
 
+// Launches of the split path's x1 pencils have n0 rows of workgroups per component, and
+// a launch at most 65536 of them.
+static int check_pass(const SpectralSizes& z) {
+  const size_t one = 3 * size_t(z.n0) * z.n1 * (z.H + 1) * z.cb;
+  for (int count : {2, 11, 181, 100000}) {
+    const int k = fields_per_pass(one, count, z.n0);
+    if (k < 1 || k > count || (k > 1 && (3LL * k * z.n0 > 65536 || k * one > size_t(96) << 20))) return 5;
+  }
+  return 0;
+}
+
 int main() {
   const size_t lds = 160 * 1024;
   std::vector<int> len;
@@ -51,7 +62,10 @@ int main() {
         for (int n2 : len) {
           if (n2 % 2) continue;
           if (3LL * n0 * n1 * n2 >= 1LL << 31) break;
-          if (const int rc = check({n0, n1, n2 / 2, cb, lds})) {
+          const SpectralSizes z{n0, n1, n2 / 2, cb, lds};
+          int rc = check(z);
+          if (!rc) rc = check_pass(z);
+          if (rc) {
             std::printf("%d x %d x %d, %zu bytes: %d\n", n0, n1, n2, cb, rc);
             return 1;
           }

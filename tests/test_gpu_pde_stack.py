@@ -37,3 +37,19 @@ def test_stack_passes(n, nt, dtype):
         want += w * float((Lv.double() * v[k].double()).sum()) * (2 * math.pi) ** 3 / (n[0] * n[1] * n[2])
     assert E == pytest.approx(want, rel=1e-6 if dtype == torch.float32 else 1e-12, abs=0)
     R.close()
+
+
+def test_stack_on_the_split_path_with_a_long_first_axis():
+    """128 x 8 x 8, 181 time points, split passes: the x1 pencils of all fields would be
+    more than a launch's second dimension holds."""
+    n, nt, dtype = (128, 8, 8), 180, torch.float64
+    gen = torch.Generator(device="cuda:0").manual_seed(5)
+    v = torch.randn((nt + 1, 3, *n), generator=gen, device="cuda:0", dtype=dtype) * 1e-3
+    R = Registration(n, nt, 0.02, 2, 1e30, dtype=dtype)
+    R.set_option("fft.force_split", 1)
+    R.set_images(T(phantom(n, 4, (1.5, 3.0), False, 1), dtype), T(phantom(n, 4, (1.5, 3.0), False, 2), dtype))
+    g, _ = R.pde_gradient(v, False)
+    for k in range(nt + 1):
+        Lv = R.apply_L(v[k].contiguous())
+        assert float((g[k] - 2 * Lv).norm()) <= 1e-12 * float(Lv.norm())
+    R.close()
