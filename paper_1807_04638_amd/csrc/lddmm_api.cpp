@@ -1399,7 +1399,7 @@ class Engine {
       drop_graph();
       return 0;
     } else if (k == "stencil.segments") {
-      if (value != 0 && !row_segments_valid(g.n2, int(value)))
+      if (value != 0 && (value < 0 || value > 4 || !row_segments_valid(g.n2, int(value))))
         return fail(LDDMM_EINVAL, "stencil.segments: 0, 2, or 4 with N2 up to 128, dividing N2");
       (void)hipStreamSynchronize(st);
       g.segvec = int(value);

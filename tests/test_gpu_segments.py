@@ -54,3 +54,11 @@ def test_default_and_refused_widths():
     assert R.get_option("stencil.segments") == 2
     with pytest.raises(LddmmError):
         R.set_option("stencil.segments", 4)  # cut rows take width 2 only
+
+
+def test_widths_beyond_32_bits_are_refused():
+    R, _ = make((4, 6, 100), torch.float32, nt=1)
+    for bad in ((1 << 32) + 2, -(1 << 32) + 4):
+        with pytest.raises(LddmmError):
+            R.set_option("stencil.segments", bad)
+    assert R.get_option("stencil.segments") == 4
