@@ -76,8 +76,9 @@ struct alignas(sizeof(T) * VR) RVec {
 };
 
 // Bound by memory (10 us of it two launches).  us with 16-byte reads, in brackets with one
-// element each, of 3 x 128^3 FP32 13.0 (15.4), 3 x 256^3 57.5 (74), 3 x 180 x 216 x 180
-// FP64 49 (46); two reads of each operand in flight, four were 13.0, 61 and 50.
+// element each, of 3 x 128^3 FP32 13.0 (15.4), 3 x 256^3 57.5 (74): wide; of FP64 3 x 128^3
+// 22.3 (21.3), 3 x 180 x 216 x 180 63 (59): one element. Two reads of each operand in
+// flight; four were 13.0 and 61 in FP32.
 template <typename T, int VR>
 __global__ void __launch_bounds__(RT) k_dot(const T* __restrict__ a, const T* __restrict__ b, long long n,
                                             double* __restrict__ partials) {
@@ -307,8 +308,8 @@ template <typename T>
 void launch_dot(const T* a, const T* b, long long n, double* partials, double* out, hipStream_t st,
                 Profiler* prof) {
   KernelTimer t(prof, "dot");
-  constexpr int W = 16 / sizeof(T);
-  const bool wide = aligned16(a) && aligned16(b);
+  constexpr int W = sizeof(T) == 4 ? 4 : 1;  // FP64 one element per read (k_dot)
+  const bool wide = W > 1 && aligned16(a) && aligned16(b);
   const unsigned nb = red_blocks(n, wide ? W : 1);
   if (wide)
     LDDMM_LAUNCH(t.start, nullptr, (k_dot<T, W>), nb, RT, 0, st, a, b, n, partials);
