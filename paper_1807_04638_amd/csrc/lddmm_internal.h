@@ -49,8 +49,6 @@ struct KernelTimer {
   }
 };
 
-#define LDDMM_COMMA ,
-
 // Launch `kern` on stream `st`; with timer events the dispatch records them.
 #define LDDMM_LAUNCH(ev0, ev1, kern, grid, block, shmem, st, ...)                             \
   do {                                                                                         \

@@ -36,7 +36,6 @@ struct Geo {
   T inv2h[3];
   FieldTiling ft;
   RowSegments seg;  // rows cut into 32-lane segments (the HALO kernels)
-  int pair;  // launch the PAIR row-vectorised kernels: a wave holds two x1 rows (see VNbr)
 };
 
 template <typename T>
@@ -51,7 +50,6 @@ Geo<T> make_geo(const Grid& g) {
   o.inv2h[2] = T(0.5 / g.h2);
   o.ft = make_field_tiling(g);
   o.seg = row_segments(g.n2);
-  o.pair = 0;
   return o;
 }
 
@@ -846,7 +844,6 @@ RowShape<T> row_shape(const Grid& g) {
   // 32 lanes per row: a wave holds rows (i1, i1 + 1) with i1 even; with N1 even
   // both rows of every wave exist
   s.pair = s.geo.ft.BX == 32 && s.geo.ft.BY % 2 == 0 && g.n1 % 2 == 0 && g.pair_rows;
-  s.geo.pair = s.pair;
   s.grid = dim3(s.geo.ft.blocks);
   s.block = dim3(s.geo.ft.BX, s.geo.ft.BY);
   return s;
