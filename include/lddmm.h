@@ -292,8 +292,9 @@ int lddmm_profile_read(lddmm_ctx* ctx, const char** names, int64_t* counts, doub
  *                                           transform and splits them after.  Where a half does
  *                                           not fit the LDS, four or three units (rows x1 mod 4
  *                                           or 3) in the same way.  Needs such a divisor of N1,
- *                                           no plane walk and an even fft.pencil_tb; otherwise
- *                                           whole planes are used.  Default 1
+ *                                           no plane walk, an even fft.pencil_tb and room in the
+ *                                           LDS for the pencils of a group of units; otherwise
+ *                                           whole planes or the split path.  Default 1
  *   "fft.plane_halves_used" read-only: 1 if planes are cut so
  *   "fft.fused"           read-only: 1 if the fused plane path is in use
  *   "fft.static_kernels"  read-only: number of passes using compile-time kernels

@@ -1228,8 +1228,8 @@ int spectral_configure(SpectralPlan<T>& sp, const FftTuning& tune, std::string& 
     return LDDMM_EUNSUPPORTED;
   }
   if ((plane_rt || pencil_rt) && size_t(n0) * n1 * M * cb >= size_t(1) << 32) {
-    // the run-time kernels' offsets inside a component (its context would not fit
-    // the device's memory)
+    // the run-time kernels' offsets inside a component (FP64 grids of 358 million voxels
+    // and more, whose contexts of 36 vector fields, 309 GB, the device does not hold)
     err = "one component's spectrum exceeds 4 GiB";
     return LDDMM_EUNSUPPORTED;
   }
@@ -1286,10 +1286,10 @@ int spectral_configure(SpectralPlan<T>& sp, const FftTuning& tune, std::string& 
 
 // Threads of a run-time plane workgroup for units of `values` complex values: 1024
 // where at most two units share a compute unit's LDS (180 x 210 x 180 FP32, 76 KB:
-// 59 + 51 us a pass against 66 + 56 with 512; FP64, 153 KB: 129 + 113 against 136 +
-// 118), 512 below (128^3 FP64, 66 KB: 28.5 us against 33 with 1024; 160 x 140 x 150
-// FP32, 42 KB: 31 against 33 with 1024 and 40 with 256), 256 for units of a few rounds
-// (60 x 84 x 70: equal to 512, and 20 % faster than 1024).
+// 55 + 53 us a pass against 58 + 57 with 512; FP64, 153 KB: 115 + 103 against 121 +
+// 107), 512 below (128^3 FP64, 66 KB: 28.5 us against 34 with 1024; 160 x 140 x 150
+// FP32, 42 KB: 30 + 27 against 31 + 29 with 1024 and 37 + 34 with 256), 256 for units of
+// a few rounds (60 x 84 x 70 FP32: equal to 512, 8.8 + 7.1 against 10.4 + 8.7 with 1024).
 template <typename T>
 int rt_plane_threads(size_t values) {
   return values * sizeof(cplx<T>) > 72 * 1024 ? 1024 : values > 1536 ? 512 : 256;
@@ -1305,9 +1305,7 @@ FftTuning default_tuning(const SpectralPlan<T>& sp) {
   // keeps this start unless another shape is clearly faster
   t.plane_threads = 1024;
   t.pencil_threads = 256;
-  // half planes where compile-time kernels exist (spectral_configure falls back
-  // to whole planes otherwise)
-  t.plane_halves = 1;
+  t.plane_halves = 1;  // the plan's units; whole planes or the split path where it has none
   void *f = nullptr, *i = nullptr, *ia = nullptr;
   plane_static_halves<T, 512>(sp.p2, sp.p1u, f, i, ia);
   if (f) {
@@ -1326,8 +1324,8 @@ FftTuning default_tuning(const SpectralPlan<T>& sp) {
   return t;
 }
 
-// Plans and the host image of the tables (`units`: with those of cut planes); device pointers are offsets into
-// the table block until spectral_place_tables sets its base.
+// Plans and the host image of the tables (`units`: with those of cut planes); device
+// pointers are offsets into the table block until spectral_place_tables sets its base.
 template <typename T>
 int spectral_plan_tables(SpectralPlan<T>& sp, const int n[3], size_t max_lds, bool units, std::string& err,
                          TableBlob& blob, size_t off[12]) {
@@ -1352,12 +1350,12 @@ int spectral_plan_tables(SpectralPlan<T>& sp, const int n[3], size_t max_lds, bo
   if (sp.xs > 1 && !make_plan(n[1] / sp.xs, sp.p1u)) sp.xs = 1;
   // Axes that no compile-time kernel transforms take the run-time kernels' plans of
   // the fewest stages: one exchange through the LDS and one barrier less where 2 5 5
-  // becomes 5 10 or 8 2 3 becomes 6 8 (K at 100 x 96 x 100 FP32 46.5 -> 40.2 us, 128 x
-  // 120 x 140 FP64 98 -> 88, 180 x 210 x 180 FP32 154 -> 143).  Radices 12 to 16 only
-  // for planes whose units leave room for one workgroup per compute unit (180 x 210 x
-  // 180 FP64 planes 118 + 108 -> 113 + 99 us); with two (FP32, 76 KB) their registers
-  // cost the second one (52 + 51 -> 65 + 64), and the pencils, which transform a pair
-  // at a time, would spill (144 points FP32 17.5 -> 25.3).
+  // becomes 5 10 or 8 2 3 becomes 6 8 (K at 100 x 96 x 100 FP32 46.7 -> 41.0 us, 128 x
+  // 120 x 140 FP64 98 -> 88, 180 x 210 x 180 FP32 155 -> 148, FP64 310 -> 283).  Radices
+  // 12 to 16 only for planes whose units leave room for one workgroup per compute unit
+  // (180 x 210 x 180 FP64 planes 128 + 114 -> 112 + 103 us); with two (FP32, 76 KB) their
+  // registers cost the second one (52 + 51 -> 65 + 64), and the pencils, which transform
+  // a pair at a time, would spill (144 points FP32 17.5 -> 25.3).
   void* f[3] = {nullptr, nullptr, nullptr};
   if (sp.xs == 2) plane_static_halves<T, 512>(sp.p2, sp.p1u, f[0], f[1], f[2]);
   if (!f[0]) plane_static<T, 512, false>(sp.p2, sp.p1, f[0], f[1], f[2]);
