@@ -1308,11 +1308,12 @@ FftTuning default_tuning(const SpectralPlan<T>& sp) {
   t.plane_halves = 1;  // the plan's units; whole planes or the split path where it has none
   void *f = nullptr, *i = nullptr, *ia = nullptr;
   plane_static_halves<T, 512>(sp.p2, sp.p1u, f, i, ia);
+  if (!f && sp.xs == 1) plane_static<T, 512, false>(sp.p2, sp.p1, f, i, ia);
   if (f) {
     // small FP32 half planes (up to 64 x 65 complex) run best with 512 threads
     if (sizeof(T) == 4 && size_t(sp.n1 / 2) * sp.M <= size_t(64) * 65) t.plane_threads = 512;
   } else {
-    t.plane_threads = rt_plane_threads<T>(size_t(sp.n1 / (sp.xs > 1 ? sp.xs : 1)) * sp.H);
+    t.plane_threads = rt_plane_threads<T>(size_t(sp.n1 / sp.xs) * sp.H);
   }
   const SpectralSizes z{sp.n0, sp.n1, sp.H, cb, sp.max_lds};
   t.pencil_tb = default_pencil_tb(z);

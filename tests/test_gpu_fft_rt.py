@@ -118,3 +118,14 @@ def test_split_grids_keep_the_compile_time_rows():
     R, p = make(n, dtype, alpha=0.0025)
     assert (R.get_option("fft.fused"), R.get_option("fft.static_kernels")) == (0, 2)
     operators_match(R, p, n, dtype)
+
+
+@pytest.mark.parametrize("n, dtype", [((6000, 16, 16), torch.float32), ((3000, 32, 32), torch.float64)])
+def test_whole_planes_of_a_long_grid_keep_their_compile_time_kernels(n, dtype):
+    """Pencils of two sequences do not fit the LDS: planes stay whole."""
+    R, p = make(n, dtype, nt=1, alpha=0.0025)
+    assert [R.get_option("fft." + k) for k in ("fused", "plane_halves_used", "static_kernels")] == [1, 0, 1]
+    f = np.random.default_rng(3).standard_normal(n)
+    f = rounded(f, dtype)
+    assert rel(R.apply_K(T(f, dtype)), O.apply_K(f, p)) <= TOL[dtype]["op"]
+    R.close()
